@@ -19,6 +19,27 @@ int hip_fail(hipError_t e, const char *what)
     return e == hipErrorOutOfMemory ? FE_ENOMEM : FE_EHIP;
 }
 
+// Two 256-thread workgroups of the FP64 passes fit a CU, 512 the chip.  Layers cost
+// 3.8 us each while two workgroups share a CU, a workgroup's start and end about
+// 6 us, so a grid that one round of workgroups can cover gets just enough layers
+// per tile for that (J v, us at 1 / 2 / 3 / 4 / 8 layers: 32^3 13.8 13.2 15.0 17.1
+// 26.3, 40^3 21.3 17.4 20.9, 48^3 32.3 28.7 29.5 26.3 27.7, 64^3 63.1 50.4 50.6
+// 45.0 42.8).  Larger grids take 8 layers, or 16 where eight rounds or more keep the
+// last one's share small (96^3, 4 / 8 / 16 layers: 134 126 137; 160x160x320: 1181
+// 1093 1056).
+int elem_layers(int nx, int ny, int nz)
+{
+    const int64_t round = 512;
+    const int64_t cols = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
+    if (cols <= round) {
+        const int64_t chunks = round / cols, tz = (nz + chunks - 1) / chunks;
+        if (tz <= 16) return (int)tz;
+    }
+    const int most = cols * ((nz + 15) / 16) >= 8 * round ? 16 : 8;
+    const int chunks = (nz + most - 1) / most;
+    return (nz + chunks - 1) / chunks;
+}
+
 Geo make_geo(const fe_grid &g, const fe_phys &ph)
 {
     Geo o;
@@ -28,6 +49,8 @@ Geo make_geo(const fe_grid &g, const fe_phys &ph)
     o.ntx = (g.nx + TX - 1) / TX;
     o.nty = (g.ny + TY - 1) / TY;
     o.ntz = (g.nz + TZ - 1) / TZ;
+    o.etz = elem_layers(g.nx, g.ny, g.nz);
+    o.ent = (g.nz + o.etz - 1) / o.etz;
     o.h = g.h;
     o.Pr = ph.Pr;
     o.B = ph.Gr * ph.Pr * ph.Pr;
@@ -119,7 +142,7 @@ int problem_create_ex(const fe_grid *grid, const fe_phys *phys, const uint8_t *d
         delete p;
         return hip_fail(e, "hipGetDevice");
     }
-    const size_t slot_bytes = (size_t)n_tiles(p->geo) * BOXN * NF * sizeof(double);
+    const size_t slot_bytes = (size_t)n_slots(*grid) * sizeof(double);
     if ((e = dalloc(p, &p->nmask, p->nn)) != hipSuccess ||
         (e = dalloc(p, &p->dof_mask, p->ndof)) != hipSuccess ||
         (e = dalloc(p, &p->slots, slot_bytes)) != hipSuccess ||

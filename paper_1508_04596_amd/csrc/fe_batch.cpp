@@ -184,7 +184,7 @@ void emit_op(Planner &P, uint64_t k, MgLevel &L, const T *x, T *t)
         return;
     }
     const BElem<T, T> a{L.geo, state_of<T>(L), x, L.gamma, L.s, L.nmask, t, (T *)L.slots};
-    P.add(k, kd<T>(K_EJV_DD, K_EJV_FF), a, belem_blocks(L.geo));
+    P.add(k, kd<T>(K_EJV_DD, K_EJV_FF), a, belem_blocks<T>(L.geo));
     P.add(k + 1, kd<T>(K_CJV_DD, K_CJV_FF), a, bnode_blocks(L.geo));
 }
 
@@ -214,7 +214,7 @@ void emit_sweep(Planner &P, uint64_t k, MgLevel &L, const T *D, const T *b, T *x
     }
     const BElemSmooth<T> a{L.geo, state_of<T>(L), cur, L.gamma, L.s, L.nmask, t, (T *)L.slots, D, b,
                            om};
-    P.add(k, kd<T>(K_ESM_D, K_ESM_F), a, belem_blocks(L.geo));
+    P.add(k, kd<T>(K_ESM_D, K_ESM_F), a, belem_blocks<T>(L.geo));
     P.add(k + 1, kd<T>(K_CSM_D, K_CSM_F), a, bnode_blocks(L.geo));
 }
 
@@ -381,7 +381,7 @@ void BatchEngine::plan(Solve &S)
         if (S.need_true && !(J.its >= J.max_its && !S.est_conv)) {
             const fe_problem *p = J.p;
             const BElem<double, double> a{p->geo, J.xlin, J.x, J.gamma, J.s, p->nmask, J.tmp, p->slots};
-            P.add(key(0, 0, 5), K_EJV_DD, a, belem_blocks(p->geo));
+            P.add(key(0, 0, 5), K_EJV_DD, a, belem_blocks<double>(p->geo));
             P.add(key(0, 0, 6), K_CJV_DD, a, bnode_blocks(p->geo));
             P.add(key(0, 0, 7), K_AXPBY, BAxpby{n, 1.0, J.b, -1.0, J.tmp}, belt_blocks(n));
             emit_norm_scale(P, 8, J, res, J.tmp, J.V);
@@ -395,7 +395,7 @@ void BatchEngine::plan(Solve &S)
             float *zj = J.Z32 + (int64_t)S.j * n;
             emit_vcycle<float>(P, J.mg, vj, zj);
             const BElem<float, double> a{p->geo, J.x32, zj, J.gamma, J.s, p->nmask, vn, p->slots};
-            P.add(key(3, 0, 0), K_EJV_FD, a, belem_blocks(p->geo));
+            P.add(key(3, 0, 0), K_EJV_FD, a, belem_blocks<float>(p->geo));
             P.add(key(3, 0, 1), K_CJV_FD, a, bnode_blocks(p->geo));
         } else if (J.pc32) {
             // FP32 V-cycle into the FP32 column, widened into the (otherwise
@@ -405,13 +405,13 @@ void BatchEngine::plan(Solve &S)
             emit_vcycle<float>(P, J.mg, vj, zj);
             P.add(key(2, MAXD, 50), K_WIDEN, BWiden{zj, zw, n}, belt_blocks(n));
             const BElem<double, double> a{p->geo, J.xlin, zw, J.gamma, J.s, p->nmask, vn, p->slots};
-            P.add(key(3, 0, 0), K_EJV_DD, a, belem_blocks(p->geo));
+            P.add(key(3, 0, 0), K_EJV_DD, a, belem_blocks<double>(p->geo));
             P.add(key(3, 0, 1), K_CJV_DD, a, bnode_blocks(p->geo));
         } else {
             double *zj = J.Z + (int64_t)S.j * n;
             emit_vcycle<double>(P, J.mg, vj, zj);
             const BElem<double, double> a{p->geo, J.xlin, zj, J.gamma, J.s, p->nmask, vn, p->slots};
-            P.add(key(3, 0, 0), K_EJV_DD, a, belem_blocks(p->geo));
+            P.add(key(3, 0, 0), K_EJV_DD, a, belem_blocks<double>(p->geo));
             P.add(key(3, 0, 1), K_CJV_DD, a, bnode_blocks(p->geo));
         }
         emit_dgs(P, J, res, S.j, true);
@@ -818,7 +818,7 @@ int jvp_batch_build(fe_batch *B, int n, fe_problem *const *probs, const void *co
         fe_problem *p = probs[i];
         tab[i] = BElem<T, T>{p->geo, (const T *)x[i], (const T *)v[i], gamma[i], s[i], p->nmask,
                              (T *)jv[i], (T *)p->slots};
-        oe[i + 1] = oe[i] + belem_blocks(p->geo);
+        oe[i + 1] = oe[i] + belem_blocks<T>(p->geo);
         oc[i + 1] = oc[i] + bnode_blocks(p->geo);
     }
     const size_t tb = (sizeof(BElem<T, T>) * n + 255) / 256 * 256, ob = sizeof(int) * (n + 1);

@@ -61,7 +61,9 @@ struct BElemSmooth {
     const T *D, *b;
     T omega;
 };
-inline int belem_blocks(const Geo &g) { return (int)n_tiles(g); }
+// workgroups of an element pass in the arithmetic of T
+template <typename T>
+inline int belem_blocks(const Geo &g) { return (int)(sizeof(T) == 8 ? n_etiles(g) : n_tiles(g)); }
 inline int bnode_blocks(const Geo &g) { return (int)((n_nodes(g) + 255) / 256); }
 template <typename Tin, typename Tout>
 hipError_t blaunch_elem_jv(const BLaunch &L, hipStream_t st);
@@ -69,6 +71,13 @@ template <typename Tin, typename Tout>
 hipError_t blaunch_combine_jv(const BLaunch &L, hipStream_t st);
 template <typename T>
 hipError_t blaunch_elem_smooth_pass(const BLaunch &L, hipStream_t st);
+// FP64 passes: fe_elem64.hip
+template <>
+hipError_t blaunch_elem_jv<double, double>(const BLaunch &L, hipStream_t st);
+template <>
+hipError_t blaunch_elem_smooth_pass<double>(const BLaunch &L, hipStream_t st);
+template <>
+hipError_t blaunch_elem_smooth_pass<float>(const BLaunch &L, hipStream_t st);
 template <typename T>
 hipError_t blaunch_combine_smooth(const BLaunch &L, hipStream_t st);
 

@@ -1,4 +1,7 @@
-// Element kernels of the stabilised natural-convection operator on gfx950.
+// Element kernels of the stabilised natural-convection operator on gfx950: the
+// FP32 operator passes, the shared-node passes of both precisions (the FP64
+// operator passes are in fe_elem64.hip), the design derivative, the nodal blocks
+// and the element Jacobians.
 //
 // One workgroup (256 threads, 4 wave64) owns a tile of 8x8x4 elements, one
 // element per thread.  The tile's 9x9x5 node box of the state (and of the
@@ -22,13 +25,10 @@
 // Brinkman limits; its variation with the element velocity vector enters the
 // consistent Jacobian).  The viscous second derivative is left out of the
 // strong residual used by SUPG/PSPG.
-#include "fe_batch.h"
-#include "fe_internal.h"
+#include "fe_elem_dev.h"
 
 namespace fe {
 namespace {
-
-constexpr double QG = 0.57735026918962576451;  // Gauss abscissa 1/sqrt(3)
 
 // Gauss loop rolled (run-time signs) by default: the unrolled form (compile-time
 // signs, fewer instructions) needs more registers than a wave64 can hold
@@ -80,23 +80,6 @@ __device__ __forceinline__ EC<T> make_ec(const Geo &g)
     c.g3 = (T)(g.gs * 0.125 * QG / 3.0);
     c.igs = (T)g.igs;
     return c;
-}
-
-// Material interpolation (Eqs. conducint, alphaint) and derivatives.
-__device__ __forceinline__ double alpha_of(const Geo &g, double y) { return g.amax * (1.0 - y) / (1.0 + g.qa * y); }
-__device__ __forceinline__ double K_of(const Geo &g, double y)
-{
-    return (y * (g.Ck * (1.0 + g.qf) - 1.0) + 1.0) / (g.Ck * (1.0 + g.qf * y));
-}
-__device__ __forceinline__ double dalpha_of(const Geo &g, double y)
-{
-    double d = 1.0 + g.qa * y;
-    return -g.amax * (1.0 + g.qa) / (d * d);
-}
-__device__ __forceinline__ double dK_of(const Geo &g, double y)
-{
-    double d = 1.0 + g.qf * y;
-    return (1.0 + g.qf) * (g.Ck - 1.0) / (g.Ck * d * d);
 }
 
 __device__ __forceinline__ float rsqrt_t(float a) { return 1.0f / sqrtf(a); }
@@ -386,32 +369,13 @@ struct TileIdx {
     int nb[8];           // node-box index of the element's corners
 };
 
-#ifndef FE_XCD_REMAP
-#define FE_XCD_REMAP 1
-#endif
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).
-// Map workgroup b to a tile so that every XCD works through a contiguous range
-// of tiles: neighbouring tiles, which re-read each other's face nodes, then
-// share an L2.  A bijection on [0, n): the last n mod 8 tiles map to themselves.
-__device__ __forceinline__ int xcd_tile(int b, int n)
-{
-    const int q = n >> 3;
-    if (b >= (q << 3)) return b;
-    return (b & 7) * q + (b >> 3);
-}
-
 // blk / nblk: this workgroup's index among the nblk workgroups that cover the
 // grid's tiles (blockIdx.x / gridDim.x, or the local index within one problem
 // of a batched launch)
 __device__ __forceinline__ TileIdx tile_index(const Geo &g, int blk, int nblk)
 {
     TileIdx t;
-#if FE_XCD_REMAP
     t.tile = xcd_tile(blk, nblk);
-#else
-    (void)nblk;
-    t.tile = blk;
-#endif
     t.btx = t.tile % g.ntx;
     int r = t.tile / g.ntx;
     t.bty = r % g.nty;
@@ -433,11 +397,6 @@ __device__ __forceinline__ TileIdx tile_index(const Geo &g, int blk, int nblk)
 __device__ __forceinline__ TileIdx tile_index(const Geo &g)
 {
     return tile_index(g, (int)blockIdx.x, (int)gridDim.x);
-}
-
-__device__ __forceinline__ int64_t gnode(const Geo &g, int I, int J, int K)
-{
-    return (int64_t)I + (int64_t)(g.nx + 1) * ((int64_t)J + (int64_t)(g.ny + 1) * K);
 }
 
 // threadIdx.x hidden from the optimiser (an empty asm statement that claims to
@@ -560,12 +519,6 @@ __device__ __forceinline__ void stage(const Geo &g, const TileIdx &t, const T *_
         stage_by_value<T, HASV, Tv>(g, t, x, v, nmask, sx, sv, (int)threadIdx.x);
     if (NVO > 0)
         for (int idx = threadIdx.x; idx < BOXN * NVO; idx += NTHR) so[idx] = T(0);
-}
-
-// Is node coordinate I (local lx) shared with the neighbouring tile in that direction?
-__device__ __forceinline__ bool shared_dir(int l, int I, int n, int T_)
-{
-    return (l == 0 && I > 0) || (l == T_ && I < n);
 }
 
 // ---- element bodies -------------------------------------------------------------
@@ -910,20 +863,19 @@ __device__ __forceinline__ void elem_jtv(const EC<T> &c, const T (*sx)[BOXN], co
 
 // ---- tile kernel: element loop + ordered LDS accumulation + face slots ---------
 
-// Tv: the direction's storage type (default the state's); it is staged as Tin.
-template <typename Tin, typename Tout, int OP, typename Tv = Tin>
-__device__ __forceinline__ void elem_tile(const Geo &g, const Tin *__restrict__ x,
-                                          const Tv *__restrict__ v,
+template <typename Tout, int OP>
+__device__ __forceinline__ void elem_tile(const Geo &g, const float *__restrict__ x,
+                                          const float *__restrict__ v,
                                           const double *__restrict__ gamma,
                                           const double *__restrict__ src,
                                           const uint8_t *__restrict__ nmask,
                                           Tout *__restrict__ out, Tout *__restrict__ slots, int blk,
                                           int nblk)
 {
-    using T = Tin;
+    using T = float;
     __shared__ TileSmem<T> S;
     const TileIdx t = tile_index(g, blk, nblk);
-    stage<T, NF, OP != OP_RES, Tv>(g, t, x, (OP == OP_RES) ? nullptr : v, nmask, S.x,
+    stage<T, NF, OP != OP_RES>(g, t, x, (OP == OP_RES) ? nullptr : v, nmask, S.x,
                  (OP == OP_RES) ? nullptr : S.v, &S.o[0][0]);
     __syncthreads();
 
@@ -993,30 +945,15 @@ __device__ __forceinline__ void elem_tile(const Geo &g, const Tin *__restrict__ 
     }
 }
 
-template <typename Tin, typename Tout, int OP>
-__global__ __launch_bounds__(NTHR) void k_elem(Geo g, const Tin *__restrict__ x,
-                                               const Tin *__restrict__ v,
-                                               const double *__restrict__ gamma,
-                                               const double *__restrict__ src,
-                                               const uint8_t *__restrict__ nmask,
-                                               Tout *__restrict__ out, Tout *__restrict__ slots)
+template <typename Tout, int OP>
+__global__ __launch_bounds__(NTHR) void k_elem32(Geo g, const float *__restrict__ x,
+                                                 const float *__restrict__ v,
+                                                 const double *__restrict__ gamma,
+                                                 const double *__restrict__ src,
+                                                 const uint8_t *__restrict__ nmask,
+                                                 Tout *__restrict__ out, Tout *__restrict__ slots)
 {
-    elem_tile<Tin, Tout, OP>(g, x, v, gamma, src, nmask, out, slots, (int)blockIdx.x,
-                             (int)gridDim.x);
-}
-
-// The FP64 operator (J v or J^T w) with the direction stored in FP32.
-template <int OP>
-__global__ __launch_bounds__(NTHR) void k_elem_dir32(Geo g, const double *__restrict__ x,
-                                                     const float *__restrict__ v,
-                                                     const double *__restrict__ gamma,
-                                                     const double *__restrict__ src,
-                                                     const uint8_t *__restrict__ nmask,
-                                                     double *__restrict__ out,
-                                                     double *__restrict__ slots)
-{
-    elem_tile<double, double, OP, float>(g, x, v, gamma, src, nmask, out, slots,
-                                         (int)blockIdx.x, (int)gridDim.x);
+    elem_tile<Tout, OP>(g, x, v, gamma, src, nmask, out, slots, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Tiles containing node coordinate I along one direction, in increasing order.
@@ -1036,6 +973,12 @@ __device__ __forceinline__ int tiles_of(int I, int n, int T_, int nt, int tl[2],
     return 1;
 }
 
+// Tiling along z of the element pass in the arithmetic of T.
+template <typename T>
+__device__ __forceinline__ int pass_layers(const Geo &g) { return sizeof(T) == 8 ? g.etz : TZ; }
+template <typename T>
+__device__ __forceinline__ int pass_tiles_z(const Geo &g) { return sizeof(T) == 8 ? g.ent : g.ntz; }
+
 // Sum of the slot partials of node (I, J, K) over its cz x cy x cx tiles in the
 // fixed tile order (z, then y, then x).  The 2 x 2 x 2 candidates are unrolled,
 // absent ones loading nothing and adding zero, so that the slot loads of all
@@ -1044,7 +987,7 @@ template <typename T>
 __device__ __forceinline__ void sum_slots5(const Geo &g, const T *__restrict__ slots, const int tx[2],
                                            const int lx[2], const int ty[2], const int ly[2],
                                            const int tz[2], const int lz[2], int cx, int cy, int cz,
-                                           T acc[NF])
+                                           int layers, T acc[NF])
 {
 #pragma unroll
     for (int q = 0; q < NF; ++q) acc[q] = T(0);
@@ -1057,7 +1000,7 @@ __device__ __forceinline__ void sum_slots5(const Geo &g, const T *__restrict__ s
                 const bool use = (a < cz) && (b < cy) && (cc < cx);
                 const int64_t tile = tx[cc] + (int64_t)g.ntx * (ty[b] + (int64_t)g.nty * tz[a]);
                 const int nb = lx[cc] + BX * (ly[b] + BY * lz[a]);
-                const T *sl = slots + (tile * BOXN + nb) * NF;
+                const T *sl = slots + tile * eslot_tile(layers) + nb * NF;
                 T v[NF];
 #pragma unroll
                 for (int q = 0; q < NF; ++q) v[q] = T(0);
@@ -1071,7 +1014,8 @@ __device__ __forceinline__ void sum_slots5(const Geo &g, const T *__restrict__ s
 }
 
 // Sum the slot partials of nodes shared between tiles, in a fixed tile order.
-template <typename Tv, typename Tout, int NV, int OP>
+// Tp: the arithmetic of the pass that wrote them.
+template <typename Tp, typename Tv, typename Tout, int NV, int OP>
 __device__ __forceinline__ void combine_nodes(const Geo &g, const Tout *__restrict__ slots,
                                               const uint8_t *__restrict__ nmask,
                                               const Tv *__restrict__ v, Tout *__restrict__ out,
@@ -1087,11 +1031,12 @@ __device__ __forceinline__ void combine_nodes(const Geo &g, const Tout *__restri
     int tx[2], lx[2], ty[2], ly[2], tz[2], lz[2];
     int cx = tiles_of(I, g.nx, TX, g.ntx, tx, lx);
     int cy = tiles_of(J, g.ny, TY, g.nty, ty, ly);
-    int cz = tiles_of(K, g.nz, TZ, g.ntz, tz, lz);
+    const int layers = NV == NF ? pass_layers<Tp>(g) : TZ;
+    int cz = tiles_of(K, g.nz, layers, NV == NF ? pass_tiles_z<Tp>(g) : g.ntz, tz, lz);
     if (cx == 1 && cy == 1 && cz == 1) return;  // written by its only tile
     Tout acc[NV];
     if (NV == NF) {
-        sum_slots5<Tout>(g, slots, tx, lx, ty, ly, tz, lz, cx, cy, cz, acc);
+        sum_slots5<Tout>(g, slots, tx, lx, ty, ly, tz, lz, cx, cy, cz, layers, acc);
     } else {
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc[q] = Tout(0);
@@ -1125,12 +1070,12 @@ __device__ __forceinline__ void combine_nodes(const Geo &g, const Tout *__restri
     }
 }
 
-template <typename Tv, typename Tout, int NV, int OP>
+template <typename Tp, typename Tv, typename Tout, int NV, int OP>
 __global__ __launch_bounds__(256) void k_combine(Geo g, const Tout *__restrict__ slots,
                                                  const uint8_t *__restrict__ nmask,
                                                  const Tv *__restrict__ v, Tout *__restrict__ out)
 {
-    combine_nodes<Tv, Tout, NV, OP>(g, slots, nmask, v, out, blockIdx.x);
+    combine_nodes<Tp, Tv, Tout, NV, OP>(g, slots, nmask, v, out, blockIdx.x);
 }
 
 // The shared-node pass fused with one damped block-Jacobi sweep of the
@@ -1160,13 +1105,14 @@ __device__ __forceinline__ void combine_smooth_nodes(const Geo &g, const T *__re
     int tx[2], lx[2], ty[2], ly[2], tz[2], lz[2];
     const int cx = tiles_of(I, g.nx, TX, g.ntx, tx, lx);
     const int cy = tiles_of(J, g.ny, TY, g.nty, ty, ly);
-    const int cz = tiles_of(K, g.nz, TZ, g.ntz, tz, lz);
+    const int layers = pass_layers<T>(g);
+    const int cz = tiles_of(K, g.nz, layers, pass_tiles_z<T>(g), tz, lz);
     T tv[NF];
     if (cx == 1 && cy == 1 && cz == 1) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) tv[f] = t[NF * gn + f];
     } else {
-        sum_slots5<T>(g, slots, tx, lx, ty, ly, tz, lz, cx, cy, cz, tv);
+        sum_slots5<T>(g, slots, tx, lx, ty, ly, tz, lz, cx, cy, cz, layers, tv);
         const uint8_t m = nmask[gn];
 #pragma unroll
         for (int f = 0; f < NF; ++f)
@@ -1522,15 +1468,15 @@ __global__ __launch_bounds__(NTHR, BdCfg<T>::WAVES) void k_blockdiag(Geo g, cons
 
 // ---- batched launches: the kernels above over a table of problems -------------
 
-template <typename Tin, typename Tout>
-__global__ __launch_bounds__(NTHR) void kb_elem_jv(const BElem<Tin, Tout> *__restrict__ tab,
-                                                   const int *__restrict__ off, int n)
+template <typename Tout>
+__global__ __launch_bounds__(NTHR) void kb_elem32_jv(const BElem<float, Tout> *__restrict__ tab,
+                                                     const int *__restrict__ off, int n)
 {
     const int e = batch_entry(off, n);
-    const BElem<Tin, Tout> &a = tab[e];
+    const BElem<float, Tout> &a = tab[e];
     const int b0 = off[e];
-    elem_tile<Tin, Tout, OP_JV>(a.g, a.x, a.v, a.gamma, a.s, a.nmask, a.out, a.slots,
-                                (int)blockIdx.x - b0, off[e + 1] - b0);
+    elem_tile<Tout, OP_JV>(a.g, a.x, a.v, a.gamma, a.s, a.nmask, a.out, a.slots,
+                           (int)blockIdx.x - b0, off[e + 1] - b0);
 }
 
 template <typename Tin, typename Tout>
@@ -1539,19 +1485,18 @@ __global__ __launch_bounds__(256) void kb_combine_jv(const BElem<Tin, Tout> *__r
 {
     const int e = batch_entry(off, n);
     const BElem<Tin, Tout> &a = tab[e];
-    combine_nodes<Tin, Tout, NF, OP_JV>(a.g, a.slots, a.nmask, a.v, a.out,
-                                        blockIdx.x - (unsigned)off[e]);
+    combine_nodes<Tin, Tin, Tout, NF, OP_JV>(a.g, a.slots, a.nmask, a.v, a.out,
+                                             blockIdx.x - (unsigned)off[e]);
 }
 
-template <typename T>
-__global__ __launch_bounds__(NTHR) void kb_elem_smooth(const BElemSmooth<T> *__restrict__ tab,
-                                                       const int *__restrict__ off, int n)
+__global__ __launch_bounds__(NTHR) void kb_elem32_smooth(const BElemSmooth<float> *__restrict__ tab,
+                                                         const int *__restrict__ off, int n)
 {
     const int e = batch_entry(off, n);
-    const BElemSmooth<T> &a = tab[e];
+    const BElemSmooth<float> &a = tab[e];
     const int b0 = off[e];
-    elem_tile<T, T, OP_JV>(a.g, a.xs, (const T *)a.x, a.gamma, a.s, a.nmask, a.t, a.slots,
-                           (int)blockIdx.x - b0, off[e + 1] - b0);
+    elem_tile<float, OP_JV>(a.g, a.xs, (const float *)a.x, a.gamma, a.s, a.nmask, a.t, a.slots,
+                            (int)blockIdx.x - b0, off[e + 1] - b0);
 }
 
 template <typename T>
@@ -1686,43 +1631,65 @@ __global__ __launch_bounds__(256) void k_stencil_from_jac(Geo g, const double *_
 
 // ---- launchers ----------------------------------------------------------------------
 
+namespace {
+
+// The element pass alone, in the arithmetic of Tin.
+template <typename Tout>
+hipError_t elem_pass(ElemOp op, const Geo &g, const float *x, const float *v, const double *gamma,
+                     const double *s, const uint8_t *nmask, Tout *out, Tout *slots, hipStream_t st)
+{
+    const dim3 grid((unsigned)n_tiles(g)), block(NTHR);
+    switch (op) {
+    case OP_RES:
+        hipLaunchKernelGGL((k_elem32<Tout, OP_RES>), grid, block, 0, st, g, x, v, gamma, s, nmask,
+                           out, slots);
+        break;
+    case OP_JV:
+        hipLaunchKernelGGL((k_elem32<Tout, OP_JV>), grid, block, 0, st, g, x, v, gamma, s, nmask,
+                           out, slots);
+        break;
+    case OP_JTV:
+        hipLaunchKernelGGL((k_elem32<Tout, OP_JTV>), grid, block, 0, st, g, x, v, gamma, s, nmask,
+                           out, slots);
+        break;
+    }
+    return hipGetLastError();
+}
+hipError_t elem_pass(ElemOp op, const Geo &g, const double *x, const double *v, const double *gamma,
+                     const double *s, const uint8_t *nmask, double *out, double *slots,
+                     hipStream_t st)
+{
+    return launch_elem64_pass<double>(op, g, x, v, gamma, s, nmask, out, slots, st);
+}
+
+// The shared-node pass after an element pass in the arithmetic of Tp.
+template <typename Tp, typename Tv, typename Tout>
+hipError_t combine_pass(ElemOp op, const Geo &g, const Tout *slots, const uint8_t *nmask,
+                        const Tv *v, Tout *out, hipStream_t st)
+{
+    const dim3 grid((unsigned)((n_nodes(g) + 255) / 256)), block(256);
+    if (op == OP_RES)
+        hipLaunchKernelGGL((k_combine<Tp, Tv, Tout, NF, OP_RES>), grid, block, 0, st, g, slots,
+                           nmask, v, out);
+    else
+        hipLaunchKernelGGL((k_combine<Tp, Tv, Tout, NF, OP_JV>), grid, block, 0, st, g, slots,
+                           nmask, v, out);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 template <typename Tin, typename Tout>
 hipError_t launch_elem(ElemOp op, const Geo &g, const Tin *x, const Tin *v, const double *gamma,
                        const double *s, const uint8_t *nmask, Tout *out, Tout *slots,
                        hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const dim3 grid((unsigned)n_tiles(g)), block(NTHR);
-    const int64_t nn = n_nodes(g);
-    const dim3 cgrid((unsigned)((nn + 255) / 256)), cblock(256);
-    switch (op) {
-    case OP_RES:
-        hipLaunchKernelGGL((k_elem<Tin, Tout, OP_RES>), grid, block, 0, st, g, x, v, gamma, s,
-                           nmask, out, slots);
-        hipLaunchKernelGGL((k_combine<Tin, Tout, NF, OP_RES>), cgrid, cblock, 0, st, g,
-                           (const Tout *)slots, nmask, v, out);
-        break;
-    case OP_JV:
-        if (ev0) {
-            const hipError_t e = hipEventRecord(ev0, st);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL((k_elem<Tin, Tout, OP_JV>), grid, block, 0, st, g, x, v, gamma, s,
-                           nmask, out, slots);
-        if (ev1) {
-            const hipError_t e = hipEventRecord(ev1, st);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL((k_combine<Tin, Tout, NF, OP_JV>), cgrid, cblock, 0, st, g,
-                           (const Tout *)slots, nmask, v, out);
-        break;
-    case OP_JTV:
-        hipLaunchKernelGGL((k_elem<Tin, Tout, OP_JTV>), grid, block, 0, st, g, x, v, gamma, s,
-                           nmask, out, slots);
-        hipLaunchKernelGGL((k_combine<Tin, Tout, NF, OP_JTV>), cgrid, cblock, 0, st, g,
-                           (const Tout *)slots, nmask, v, out);
-        break;
-    }
-    return hipGetLastError();
+    hipError_t e = hipSuccess;
+    if (op == OP_JV && ev0) e = hipEventRecord(ev0, st);
+    if (e == hipSuccess) e = elem_pass(op, g, x, v, gamma, s, nmask, out, slots, st);
+    if (e == hipSuccess && op == OP_JV && ev1) e = hipEventRecord(ev1, st);
+    if (e == hipSuccess) e = combine_pass<Tin>(op, g, (const Tout *)slots, nmask, v, out, st);
+    return e;
 }
 
 template hipError_t launch_elem<double, double>(ElemOp, const Geo &, const double *, const double *,
@@ -1739,23 +1706,10 @@ hipError_t launch_elem_dir32(ElemOp op, const Geo &g, const double *x, const flo
                              const double *gamma, const double *s, const uint8_t *nmask,
                              double *out, double *slots, hipStream_t st)
 {
-    const dim3 grid((unsigned)n_tiles(g)), block(NTHR);
-    const int64_t nn = n_nodes(g);
-    const dim3 cgrid((unsigned)((nn + 255) / 256)), cblock(256);
-    if (op == OP_JV) {
-        hipLaunchKernelGGL((k_elem_dir32<OP_JV>), grid, block, 0, st, g, x, v, gamma, s, nmask,
-                           out, slots);
-        hipLaunchKernelGGL((k_combine<float, double, NF, OP_JV>), cgrid, cblock, 0, st, g,
-                           (const double *)slots, nmask, v, out);
-    } else if (op == OP_JTV) {
-        hipLaunchKernelGGL((k_elem_dir32<OP_JTV>), grid, block, 0, st, g, x, v, gamma, s, nmask,
-                           out, slots);
-        hipLaunchKernelGGL((k_combine<float, double, NF, OP_JTV>), cgrid, cblock, 0, st, g,
-                           (const double *)slots, nmask, v, out);
-    } else {
-        return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    if (op != OP_JV && op != OP_JTV) return hipErrorInvalidValue;
+    const hipError_t e = launch_elem64_pass<float>(op, g, x, v, gamma, s, nmask, out, slots, st);
+    if (e != hipSuccess) return e;
+    return combine_pass<double>(op, g, (const double *)slots, nmask, v, out, st);
 }
 
 hipError_t launch_dRdgamma(const Geo &g, const double *x, const double *lam, const double *gamma,
@@ -1773,7 +1727,7 @@ hipError_t launch_blockdiag(const Geo &g, const T *x, const double *gamma, const
     hipLaunchKernelGGL(k_blockdiag<T>, dim3((unsigned)n_tiles(g)), dim3(NTHR), 0, st, g, x, gamma,
                        s, nmask, D, slots);
     const int64_t nn = n_nodes(g);
-    hipLaunchKernelGGL((k_combine<T, T, 25, OP_RES>), dim3((unsigned)((nn + 255) / 256)),
+    hipLaunchKernelGGL((k_combine<T, T, T, 25, OP_RES>), dim3((unsigned)((nn + 255) / 256)),
                        dim3(256), 0, st, g, (const T *)slots, nmask, (const T *)nullptr, D);
     return hipGetLastError();
 }
@@ -1789,20 +1743,16 @@ hipError_t launch_elem_smooth(bool tr, const Geo &g, const T *xs, T *x, const do
                               const double *s, const uint8_t *nmask, T *t, T *slots, const T *D,
                               const T *b, T omega, hipStream_t st)
 {
-    const dim3 grid((unsigned)n_tiles(g)), block(NTHR);
-    const int64_t nn = n_nodes(g);
-    const dim3 cgrid((unsigned)((nn + 255) / 256)), cblock(256);
-    if (tr) {
-        hipLaunchKernelGGL((k_elem<T, T, OP_JTV>), grid, block, 0, st, g, xs, (const T *)x, gamma,
-                           s, nmask, t, slots);
-        hipLaunchKernelGGL((k_combine_smooth<T, OP_JTV>), cgrid, cblock, 0, st, g,
-                           (const T *)slots, nmask, (const T *)t, D, b, x, omega);
-    } else {
-        hipLaunchKernelGGL((k_elem<T, T, OP_JV>), grid, block, 0, st, g, xs, (const T *)x, gamma, s,
-                           nmask, t, slots);
-        hipLaunchKernelGGL((k_combine_smooth<T, OP_JV>), cgrid, cblock, 0, st, g,
-                           (const T *)slots, nmask, (const T *)t, D, b, x, omega);
-    }
+    const hipError_t e = elem_pass(tr ? OP_JTV : OP_JV, g, xs, (const T *)x, gamma, s, nmask, t,
+                                   slots, st);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)((n_nodes(g) + 255) / 256)), block(256);
+    if (tr)
+        hipLaunchKernelGGL((k_combine_smooth<T, OP_JTV>), grid, block, 0, st, g, (const T *)slots,
+                           nmask, (const T *)t, D, b, x, omega);
+    else
+        hipLaunchKernelGGL((k_combine_smooth<T, OP_JV>), grid, block, 0, st, g, (const T *)slots,
+                           nmask, (const T *)t, D, b, x, omega);
     return hipGetLastError();
 }
 template hipError_t launch_elem_smooth<double>(bool, const Geo &, const double *, double *,
@@ -1844,8 +1794,8 @@ template <typename Tin, typename Tout>
 hipError_t blaunch_elem_jv(const BLaunch &L, hipStream_t st)
 {
     if (L.blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL((kb_elem_jv<Tin, Tout>), dim3((unsigned)L.blocks), dim3(NTHR), 0, st,
-                       (const BElem<Tin, Tout> *)L.tab, L.off, L.n);
+    hipLaunchKernelGGL((kb_elem32_jv<Tout>), dim3((unsigned)L.blocks), dim3(NTHR), 0, st,
+                       (const BElem<float, Tout> *)L.tab, L.off, L.n);
     return hipGetLastError();
 }
 
@@ -1858,12 +1808,12 @@ hipError_t blaunch_combine_jv(const BLaunch &L, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t blaunch_elem_smooth_pass(const BLaunch &L, hipStream_t st)
+template <>
+hipError_t blaunch_elem_smooth_pass<float>(const BLaunch &L, hipStream_t st)
 {
     if (L.blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL((kb_elem_smooth<T>), dim3((unsigned)L.blocks), dim3(NTHR), 0, st,
-                       (const BElemSmooth<T> *)L.tab, L.off, L.n);
+    hipLaunchKernelGGL(kb_elem32_smooth, dim3((unsigned)L.blocks), dim3(NTHR), 0, st,
+                       (const BElemSmooth<float> *)L.tab, L.off, L.n);
     return hipGetLastError();
 }
 
@@ -1876,14 +1826,11 @@ hipError_t blaunch_combine_smooth(const BLaunch &L, hipStream_t st)
     return hipGetLastError();
 }
 
-template hipError_t blaunch_elem_jv<double, double>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_elem_jv<float, double>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_elem_jv<float, float>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_combine_jv<double, double>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_combine_jv<float, double>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_combine_jv<float, float>(const BLaunch &, hipStream_t);
-template hipError_t blaunch_elem_smooth_pass<double>(const BLaunch &, hipStream_t);
-template hipError_t blaunch_elem_smooth_pass<float>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_combine_smooth<double>(const BLaunch &, hipStream_t);
 template hipError_t blaunch_combine_smooth<float>(const BLaunch &, hipStream_t);
 

@@ -29,11 +29,14 @@ constexpr int TX = FE_TILE_X, TY = FE_TILE_Y, TZ = FE_TILE_Z;
 constexpr int NTHR = TX * TY * TZ;  // 256 threads = 4 wave64
 constexpr int BX = TX + 1, BY = TY + 1, BZ = TZ + 1;
 constexpr int BOXN = BX * BY * BZ;  // nodes of the tile's node box (405)
+constexpr int PNODE = BX * BY;      // nodes of a tile's node plane (81)
+constexpr int PVAL = PNODE * NF;    // their values (405)
 
 // Grid geometry and physical constants, passed by value to every element kernel.
 struct Geo {
     int nx, ny, nz;     // elements
     int ntx, nty, ntz;  // tiles
+    int etz, ent;       // FP64 operator passes: element layers per tile, tiles along z
     double h, Pr, B;    // B = Gr * Pr^2 (buoyancy coefficient)
     double eg[3];
     double Ck, qf, amax, qa;
@@ -54,6 +57,26 @@ __host__ __device__ inline int64_t n_nodes(const Geo &g)
 }
 __host__ __device__ inline int64_t n_elem(const Geo &g) { return (int64_t)g.nx * g.ny * g.nz; }
 inline int64_t n_tiles(const Geo &g) { return (int64_t)g.ntx * g.nty * g.ntz; }
+// The FP64 operator passes (fe_elem64.hip) march through tiles of 8 x 8 x etz
+// elements, the FP32 ones work on tiles of 8 x 8 x 4.  A tile of L layers has
+// L + 1 node planes of PVAL tile-face partial sums.
+inline int64_t n_etiles(const Geo &g) { return (int64_t)g.ntx * g.nty * g.ent; }
+__host__ __device__ inline int64_t eslot_tile(int layers) { return (int64_t)PVAL * (layers + 1); }
+// Layers per tile of the FP64 passes on an nx x ny x nz grid.
+int elem_layers(int nx, int ny, int nz);
+// Values of the slots of one FP64 pass, of one FP32 pass, and of a buffer for both.
+inline int64_t n_slots64(const fe_grid &g)
+{
+    const int tz = elem_layers(g.nx, g.ny, g.nz);
+    return (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + tz - 1) / tz) *
+           eslot_tile(tz);
+}
+inline int64_t n_slots32(const fe_grid &g)
+{
+    return (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + TZ - 1) / TZ) *
+           eslot_tile(TZ);
+}
+inline int64_t n_slots(const fe_grid &g) { return std::max(n_slots64(g), n_slots32(g)); }
 
 // The nodal 5x5 blocks ([node][25], row-major) of the 256 consecutive nodes
 // n0 .. n0 + 255 copied to LDS with coalesced loads, for kernels that run one
@@ -87,13 +110,19 @@ enum ElemOp { OP_RES = 0, OP_JV = 1, OP_JTV = 2 };
 // ---- element kernel launchers (fe_elem.hip) --------------------------------
 // x, v: node vectors of type Tin; out: node vector of type Tout; nmask: per
 // node bit mask (bit f set = DOF f prescribed); slots: tile-face partial sums,
-// n_tiles * BOXN * 5 values of Tout.
+// n_slots64 or n_slots32 values of Tout (by Tin).
 // ev0/ev1 (optional): recorded on st right before and right after the J v
 // element-pass kernel.
 template <typename Tin, typename Tout>
 hipError_t launch_elem(ElemOp op, const Geo &g, const Tin *x, const Tin *v, const double *gamma,
                        const double *s, const uint8_t *nmask, Tout *out, Tout *slots,
                        hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// The FP64 element pass by itself (fe_elem64.hip; it leaves the shared nodes to the
+// shared-node pass), the direction stored as Tv.
+template <typename Tv>
+hipError_t launch_elem64_pass(ElemOp op, const Geo &g, const double *x, const Tv *v,
+                              const double *gamma, const double *s, const uint8_t *nmask,
+                              double *out, double *slots, hipStream_t st);
 hipError_t launch_dRdgamma(const Geo &g, const double *x, const double *lam, const double *gamma,
                            const double *s, const uint8_t *nmask, double *gout, hipStream_t st);
 // J v (OP_JV) or J^T w (OP_JTV) in FP64 at an FP64 state x with the direction

@@ -174,7 +174,7 @@ int64_t mg_footprint_bytes(const fe_grid &g0, bool mixed, int64_t asm_nodes)
         const int64_t nt = (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + TZ - 1) / TZ);
         if (l > 0) {
             b += r256(nn) + 2 * r256(8 * ne) + r256(8 * ndof) + r256(8 * 25 * nn);
-            b += r256(nt * BOXN * NF * 8) + r256(nt * BOXN * 25 * 8);
+            b += r256(n_slots(g) * 8) + r256(nt * BOXN * 25 * 8);
             b += 2 * r256(8 * ndof);
             if (mixed) b += r256(4 * ndof) + r256(4 * 25 * nn) + 2 * r256(4 * ndof);
         } else if (mixed) {
@@ -229,7 +229,7 @@ int mg_create(fe_problem *p, bool mixed, int64_t asm_nodes, Mg **out)
             if (e == hipSuccess) e = dalloc(p, &L.s, sizeof(double) * L.ne);
             if (e == hipSuccess) e = dalloc(p, &L.x, nb);
             if (e == hipSuccess) e = dalloc(p, &L.D, sizeof(double) * 25 * L.nn);
-            if (e == hipSuccess) e = dalloc(p, &L.slots, (size_t)n_tiles(L.geo) * BOXN * NF * sizeof(double));
+            if (e == hipSuccess) e = dalloc(p, &L.slots, (size_t)n_slots(g) * sizeof(double));
             if (e == hipSuccess) e = dalloc(p, &L.slots25, (size_t)n_tiles(L.geo) * BOXN * 25 * sizeof(double));
             if (e == hipSuccess && mixed) e = dalloc(p, &L.x32, sizeof(float) * L.ndof);
             if (e == hipSuccess && mixed) e = dalloc(p, &L.D32, sizeof(float) * 25 * L.nn);

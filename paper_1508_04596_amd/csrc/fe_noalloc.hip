@@ -47,8 +47,7 @@ int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 int64_t noalloc_scratch_bytes(const fe_grid &grid, fe_prec prec)
 {
     const Geo g = make_geo(grid, fe_phys{});
-    const int64_t word = prec == FE_FP32 ? 4 : 8;
-    return round256(n_nodes(g)) + n_tiles(g) * BOXN * NF * word;
+    return round256(n_nodes(g)) + (prec == FE_FP32 ? n_slots32(grid) * 4 : n_slots64(grid) * 8);
 }
 
 }  // namespace fe

@@ -467,7 +467,7 @@ int64_t fe_solve_footprint_bytes(const fe_grid *grid, const fe_solve_opts *opts)
     auto r = [](int64_t b) { return (b + 255) / 256 * 256; };
     int64_t b = 0;
     // problem handle
-    b += r(nn) + r(ndof) + r(ntile * BOXN * NF * 8) + r((int64_t)PARTIAL_COLS * RED_BLOCKS * 8) + r(256 * 8);
+    b += r(nn) + r(ndof) + r(n_slots(*grid) * 8) + r((int64_t)PARTIAL_COLS * RED_BLOCKS * 8) + r(256 * 8);
     // solver workspace
     b += 7 * r(8 * ndof) + r(8 * ndof * (opts->restart + 1)) + r(8 * ndof * opts->restart);
     if (mixed) b += r(4 * ndof * opts->restart) + r(4 * 25 * nn) + r(4 * ndof);
