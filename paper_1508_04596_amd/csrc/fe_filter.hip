@@ -6,12 +6,25 @@
 // psi trilinear on the nodes, gamma constant per element, r = R / (2 sqrt 3).
 // Filtered element value = mean of psi over the element's nodes:
 //   F gamma = A K^-1 T gamma,  F^T g = T^T K^-1 A^T g,  K = r^2 K_lap + M.
-// K is applied matrix-free node by node (each node sums the element matrix rows
-// of its up to 8 elements; the element matrix depends only on the Hamming
-// distance between the two corners), and K psi = b is solved by Jacobi-
-// preconditioned conjugate gradients with every scalar kept on the device.
+// The element matrix depends only on the Hamming distance of the two corners, so
+// K couples a node with its 27 neighbours by four constants times the number of
+// elements that hold both, and K psi = b is solved by Jacobi-preconditioned
+// conjugate gradients with every scalar kept on the device.
+//
+// Two launches per iteration.  The first forms the direction p = z + beta p where
+// K p needs it: a workgroup stages p of a plane of its tile and the rim in LDS, whose
+// sums over the nine neighbours of a node serve three planes.  The second updates
+// the residual, and x every other time.  The partial sums of a pass are added by
+// every workgroup of the next, in the same order, in place of a launch of its own.
+// Bound: up to about 10^6 nodes the latency of a pass (5.5 us: partial sums, then
+// one plane after the other), above it memory (10 vectors per iteration; 160x160x320
+// elements at about 3.9 TB/s).  Forward and transpose at 64x64x128, 24 iterations
+// each: 2083 -> 969 us.  Before, K p gathered 64 values per node (20.7 us a pass) in
+// five launches per iteration; 18 gathers per node from global memory instead of the
+// staged plane took 15.3 us, staged 10.7.
 #include <cstring>
 
+#include "fe_elem_dev.h"
 #include "fe_topopt.h"
 
 namespace fe {
@@ -22,32 +35,6 @@ __device__ __forceinline__ int64_t fnode(const FGeo &g, int I, int J, int K)
     return (int64_t)I + (int64_t)(g.nx + 1) * ((int64_t)J + (int64_t)(g.ny + 1) * K);
 }
 
-// y = K x at node n; also the node's number of elements (for the diagonal)
-__device__ __forceinline__ double kapply(const FGeo &g, const double *__restrict__ x, int I, int J,
-                                         int K, int *nel)
-{
-    double acc = 0.0;
-    int cnt = 0;
-    for (int ez = K - 1; ez <= K; ++ez) {
-        if (ez < 0 || ez >= g.nz) continue;
-        for (int ey = J - 1; ey <= J; ++ey) {
-            if (ey < 0 || ey >= g.ny) continue;
-            for (int ex = I - 1; ex <= I; ++ex) {
-                if (ex < 0 || ex >= g.nx) continue;
-                ++cnt;
-                const int ca = (I - ex) | ((J - ey) << 1) | ((K - ez) << 2);
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    const int d = __popc(ca ^ b);
-                    acc += g.E[d] * x[fnode(g, ex + (b & 1), ey + ((b >> 1) & 1), ez + (b >> 2))];
-                }
-            }
-        }
-    }
-    *nel = cnt;
-    return acc;
-}
-
 __device__ __forceinline__ void node_ijk(const FGeo &g, int64_t n, int &I, int &J, int &K)
 {
     I = (int)(n % (g.nx + 1));
@@ -56,15 +43,9 @@ __device__ __forceinline__ void node_ijk(const FGeo &g, int64_t n, int &I, int &
     K = (int)(r / (g.ny + 1));
 }
 
-__device__ __forceinline__ int node_nel(const FGeo &g, int I, int J, int K)
-{
-    const int cx = (I > 0) + (I < g.nx), cy = (J > 0) + (J < g.ny), cz = (K > 0) + (K < g.nz);
-    return cx * cy * cz;
-}
-
-// block partial sums over a grid-stride loop: partial[j * RED_BLOCKS + blockIdx.x]
+// block partial sums: out_j[blockIdx.x], j < NV <= 2
 template <int NV>
-__device__ __forceinline__ void block_partials(double v[NV], double *partial)
+__device__ __forceinline__ void block_partials(const double *v, double *out0, double *out1)
 {
     __shared__ double red[NV][RED_THREADS / 64];
 #pragma unroll
@@ -77,7 +58,7 @@ __device__ __forceinline__ void block_partials(double v[NV], double *partial)
     if (threadIdx.x < NV) {
         double s = 0.0;
         for (int w = 0; w < RED_THREADS / 64; ++w) s += red[threadIdx.x][w];
-        partial[threadIdx.x * RED_BLOCKS + blockIdx.x] = s;
+        (threadIdx.x == 0 ? out0 : out1)[blockIdx.x] = s;
     }
 }
 
@@ -118,78 +99,242 @@ __global__ __launch_bounds__(256) void k_node_to_elem(FGeo g, const double *__re
     out[e] = scale * acc;
 }
 
-// CG start from x = 0: r = b, z = D^-1 b, p = z; partials of <r, z> and <r, r>
-__global__ __launch_bounds__(RED_THREADS) void k_cg_init(FGeo g, const double *__restrict__ b,
-                                                         double *__restrict__ x, double *__restrict__ r,
-                                                         double *__restrict__ p, double *partial)
+// Work of the CG passes: tiles of wx x wy nodes (at most 256, one per thread) times
+// cz planes, spread over at most RED_BLOCKS workgroups (one partial sum each).
+struct CgTiling {
+    int wx, wy, cz;      // nodes of a tile
+    int nx, ny, tiles;   // tiles along x and y, all tiles
+};
+constexpr int TILE_W = 40;                            // most nodes of a tile along x
+constexpr int TILE_HALO = (2 + 2) * (RED_THREADS / 2 + 2);  // largest tile with its rim (2 x 128)
+
+// This thread's node column of a tile.
+struct Column {
+    bool in;
+    int I0, J0, K0, K1;             // first node of the tile, planes
+    int I, J;
+    int64_t n, plane;               // node in its plane, nodes of a plane
+    double wxm, wxp, wym, wyp;      // 1 if there is a neighbour on that side, else 0
+    double cx, cy;                  // elements along x and y (1 or 2)
+};
+
+// First tile of workgroup b: consecutive tiles, so that neighbours share an XCD's L2.
+__device__ __forceinline__ int tile_begin(const CgTiling &t, int b)
 {
-    const int64_t nn = (int64_t)(g.nx + 1) * (g.ny + 1) * (g.nz + 1);
+    return (int)((int64_t)t.tiles * b / (int)gridDim.x);
+}
+
+__device__ __forceinline__ Column column(const FGeo &g, const CgTiling &t, int tile)
+{
+    Column c;
+    const int bx = tile % t.nx, r = tile / t.nx, by = r % t.ny, bz = r / t.ny;
+    const int ly = (int)threadIdx.x / t.wx, lx = (int)threadIdx.x - ly * t.wx;
+    c.I0 = bx * t.wx;
+    c.J0 = by * t.wy;
+    c.I = c.I0 + lx;
+    c.J = c.J0 + ly;
+    c.in = ly < t.wy && c.I <= g.nx && c.J <= g.ny;
+    c.K0 = bz * t.cz;
+    c.K1 = min(c.K0 + t.cz, g.nz + 1);
+    c.plane = (int64_t)(g.nx + 1) * (g.ny + 1);
+    c.n = c.in ? c.I + (int64_t)(g.nx + 1) * c.J : 0;
+    c.wxm = c.I > 0;
+    c.wxp = c.I < g.nx;
+    c.wym = c.J > 0;
+    c.wyp = c.J < g.ny;
+    c.cx = c.wxm + c.wxp;
+    c.cy = c.wym + c.wyp;
+    return c;
+}
+
+// Sum of nparts block partials, the same in every workgroup.
+__device__ __forceinline__ double total(const double *__restrict__ partial, int nparts)
+{
+    __shared__ double red[RED_THREADS / 64];
+    double s = 0.0;
+    for (int q = threadIdx.x; q < nparts; q += RED_THREADS) s += partial[q];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double v = 0.0;
+    for (int w = 0; w < RED_THREADS / 64; ++w) v += red[w];
+    return v;
+}
+
+// CG start from x = 0: z = D^-1 b (D = E0 times the node's elements); partials of
+// <r, z> and <r, r>.
+__global__ __launch_bounds__(RED_THREADS) void k_cg_init(FGeo g, CgTiling t, double iE0,
+                                                         const double *__restrict__ b,
+                                                         double *__restrict__ x,
+                                                         double *__restrict__ z, double *prz,
+                                                         double *prr)
+{
     double v[2] = {0.0, 0.0};
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < nn;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        int I, J, K;
-        node_ijk(g, n, I, J, K);
-        const double rn = b[n], zn = rn / (node_nel(g, I, J, K) * g.E[0]);
-        x[n] = 0.0;
-        r[n] = rn;
-        p[n] = zn;
-        v[0] += rn * zn;
-        v[1] += rn * rn;
+    const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int t1 = tile_begin(t, lb + 1);
+    for (int tile = tile_begin(t, lb); tile < t1; ++tile) {
+        const Column c = column(g, t, tile);
+        if (!c.in) continue;
+        for (int K = c.K0; K < c.K1; ++K) {
+            const int64_t n = c.n + c.plane * K;
+            const double cz = (K > 0) + (K < g.nz);
+            const double rn = b[n], zn = rn * (iE0 / (c.cx * c.cy * cz));
+            x[n] = 0.0;
+            z[n] = zn;
+            v[0] += rn * zn;
+            v[1] += rn * rn;
+        }
     }
-    block_partials<2>(v, partial);
+    block_partials<2>(v, prz, prr);
 }
 
-// y = K p, partials of <p, y>
-__global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, const double *__restrict__ p,
-                                                          double *__restrict__ y, double *partial)
+// p = z + beta p_old (z in the first iteration), y = K p, partials of <p, y>.
+// beta = rz / rz_old: rz from the last pass's nparts partials, kept in sc[cur] for the
+// passes that follow; rz_old = sc[1 - cur].
+template <bool FIRST>
+__global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, int nparts,
+                                                          const double *__restrict__ prz,
+                                                          double *sc, int cur,
+                                                          const double *__restrict__ z,
+                                                          const double *__restrict__ pold,
+                                                          double *__restrict__ p,
+                                                          double *__restrict__ y, double *ppy)
 {
-    const int64_t nn = (int64_t)(g.nx + 1) * (g.ny + 1) * (g.nz + 1);
-    double v[1] = {0.0};
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < nn;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        int I, J, K, nel;
-        node_ijk(g, n, I, J, K);
-        const double yn = kapply(g, p, I, J, K, &nel);
-        y[n] = yn;
-        v[0] += p[n] * yn;
+    __shared__ double w[2][TILE_HALO];  // p of a plane of the tile and its rim, ring of two
+    const double E0 = g.E[0], E1 = g.E[1], E2 = g.E[2], E3 = g.E[3];
+    const int sx = t.wx + 2, halo = sx * (t.wy + 2);
+    constexpr int NL = (TILE_HALO + RED_THREADS - 1) / RED_THREADS;
+    double v = 0.0, beta = 0.0;
+    bool first = true;
+    const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int t1 = tile_begin(t, lb + 1);
+    for (int tile = tile_begin(t, lb); tile < t1; ++tile) {
+        const Column c = column(g, t, tile);
+        // this thread's values of the rimmed plane (0 outside the grid)
+        int64_t off[NL];
+        bool ok[NL];
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            const int e = (int)threadIdx.x + q * RED_THREADS, hy = e / sx, hx = e - hy * sx;
+            const int I = c.I0 + hx - 1, J = c.J0 + hy - 1;
+            ok[q] = e < halo && I >= 0 && I <= g.nx && J >= 0 && J <= g.ny;
+            off[q] = ok[q] ? I + (int64_t)(g.nx + 1) * J : 0;
+        }
+        double zr[NL], pr[NL];
+        auto load = [&](int K) {
+            const int64_t b = c.plane * K;
+#pragma unroll
+            for (int q = 0; q < NL; ++q)
+                if (q * RED_THREADS < halo) {
+                    zr[q] = z[b + off[q]];
+                    pr[q] = FIRST ? 0.0 : pold[b + off[q]];
+                }
+        };
+        auto stage = [&](int b) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                const int e = (int)threadIdx.x + q * RED_THREADS;
+                if (e < halo) w[b][e] = ok[q] ? (FIRST ? zr[q] : fma(beta, pr[q], zr[q])) : 0.0;
+            }
+        };
+        // in-plane sums over the node itself, its edge neighbours and its corner
+        // neighbours, each weighted by the elements along x and y in common
+        struct Sums {
+            double a0, a1, a2, p;
+        };
+        const int me0 = ((int)threadIdx.x / t.wx + 1) * sx + (int)threadIdx.x % t.wx + 1;
+        const int m = c.in ? me0 : sx + 1;
+        auto sums = [&](int b) {
+            const double *P = w[b] + m;
+            Sums s;
+            s.p = P[0];
+            s.a0 = c.cx * c.cy * s.p;
+            s.a1 = c.cy * (P[-1] + P[1]) + c.cx * (P[-sx] + P[sx]);
+            s.a2 = (P[-sx - 1] + P[-sx + 1]) + (P[sx - 1] + P[sx + 1]);
+            return s;
+        };
+        const Sums none = {0.0, 0.0, 0.0, 0.0};
+        const int Ka = max(c.K0 - 1, 0), Kb = min(c.K1, g.nz);  // planes to stage
+        load(Ka);
+        if (first) {
+            const double rz = total(prz, nparts), old = FIRST ? 1.0 : sc[1 - cur];
+            beta = old > 0.0 ? rz / old : 0.0;
+            if (blockIdx.x == 0 && threadIdx.x == 0) sc[cur] = rz;
+            first = false;
+        } else {
+            __syncthreads();  // the last tile's planes have been read
+        }
+        Sums lo = none, me = none;
+        for (int K = Ka; K <= Kb + 1; ++K) {
+            // plane K joins; plane K - 1 is complete
+            Sums hi = none;
+            if (K <= Kb) {
+                stage(K & 1);
+                if (K < Kb) load(K + 1);
+                __syncthreads();
+                hi = sums(K & 1);
+            }
+            const int Ko = K - 1;
+            if (c.in && Ko >= c.K0 && Ko < c.K1) {
+                const double cz = (Ko > 0) + (Ko < g.nz);
+                const double yn = cz * (E0 * me.a0 + E1 * me.a1 + E2 * me.a2) +
+                                  E1 * (lo.a0 + hi.a0) + E2 * (lo.a1 + hi.a1) + E3 * (lo.a2 + hi.a2);
+                const int64_t n = c.n + c.plane * Ko;
+                p[n] = me.p;
+                y[n] = yn;
+                v += me.p * yn;
+            }
+            lo = me;
+            me = hi;
+        }
     }
-    block_partials<1>(v, partial);
+    block_partials<1>(&v, ppy, nullptr);
 }
 
-// alpha = rz / pAp; x += alpha p; r -= alpha y; partials of <r, D^-1 r> and <r, r>
-__global__ __launch_bounds__(RED_THREADS) void k_cg_step(FGeo g, const double *__restrict__ sc,
-                                                         int cur, const double *__restrict__ p,
+// alpha = rz / <p, y>; r -= alpha y, kept as z = D^-1 r; partials of <r, z> and
+// <r, r>.  x is updated every other iteration (X), with both directions at hand:
+// x += alpha_old p_old + alpha p, alpha_old as the iteration before left it in
+// sc[5] (both = 0: x += alpha p).  A zero right-hand side leaves x = 0.
+template <bool X>
+__global__ __launch_bounds__(RED_THREADS) void k_cg_step(FGeo g, CgTiling t, int nparts, double iE0,
+                                                         const double *__restrict__ ppy, double *sc,
+                                                         int cur, int both,
+                                                         const double *__restrict__ pold,
+                                                         const double *__restrict__ p,
                                                          const double *__restrict__ y,
                                                          double *__restrict__ x,
-                                                         double *__restrict__ r, double *partial)
+                                                         double *__restrict__ z, double *prz,
+                                                         double *prr)
 {
-    const int64_t nn = (int64_t)(g.nx + 1) * (g.ny + 1) * (g.nz + 1);
-    const double alpha = sc[cur] / sc[2];  // rz / pAp
+    const double py = total(ppy, nparts), rz = sc[cur];
+    const double alpha = rz == 0.0 && py == 0.0 ? 0.0 : rz / py;
+    const double before = X && both ? sc[5] : 0.0;
+    if (!X && blockIdx.x == 0 && threadIdx.x == 0) sc[5] = alpha;
     double v[2] = {0.0, 0.0};
-    for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < nn;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        int I, J, K;
-        node_ijk(g, n, I, J, K);
-        x[n] += alpha * p[n];
-        const double rn = r[n] - alpha * y[n];
-        r[n] = rn;
-        v[0] += rn * rn / (node_nel(g, I, J, K) * g.E[0]);
-        v[1] += rn * rn;
+    const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int t1 = tile_begin(t, lb + 1);
+    for (int tile = tile_begin(t, lb); tile < t1; ++tile) {
+        const Column c = column(g, t, tile);
+        if (!c.in) continue;
+        const double cxy = c.cx * c.cy;
+#pragma unroll 2
+        for (int K = c.K0; K < c.K1; ++K) {
+            const int64_t n = c.n + c.plane * K;
+            const double cnt = (K > 0 && K < g.nz) ? 2.0 * cxy : cxy;
+            if (X) {
+                double xn = fma(alpha, p[n], x[n]);
+                if (both) xn = fma(before, pold[n], xn);
+                x[n] = xn;
+            }
+            const double zn = z[n] - alpha * y[n] * (iE0 / cnt);
+            z[n] = zn;
+            const double rn = zn * (g.E[0] * cnt);
+            v[0] += rn * zn;
+            v[1] += rn * rn;
+        }
     }
-    block_partials<2>(v, partial);
-}
-
-// beta = rz_new / rz_old; p = D^-1 r + beta p
-__global__ __launch_bounds__(256) void k_cg_dir(FGeo g, const double *__restrict__ sc, int cur,
-                                                const double *__restrict__ r, double *__restrict__ p)
-{
-    const int64_t nn = (int64_t)(g.nx + 1) * (g.ny + 1) * (g.nz + 1);
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= nn) return;
-    const double beta = sc[1 - cur] / sc[cur];  // new / old
-    int I, J, K;
-    node_ijk(g, n, I, J, K);
-    p[n] = r[n] / (node_nel(g, I, J, K) * g.E[0]) + beta * p[n];
+    block_partials<2>(v, prz, prr);
 }
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -217,7 +362,7 @@ hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
     if (e == hipSuccess) e = hipMalloc(&f->r, nb);
     if (e == hipSuccess) e = hipMalloc(&f->p, nb);
     if (e == hipSuccess) e = hipMalloc(&f->y, nb);
-    if (e == hipSuccess) e = hipMalloc(&f->partial, sizeof(double) * 2 * RED_BLOCKS);
+    if (e == hipSuccess) e = hipMalloc(&f->partial, sizeof(double) * 3 * RED_BLOCKS);
     if (e == hipSuccess) e = hipMalloc(&f->sc, sizeof(double) * 8);
     if (e == hipSuccess) e = hipHostMalloc(&f->hsc, sizeof(double) * 8);
     return e;
@@ -230,40 +375,70 @@ void filter_free(Filter *f)
     if (f->hsc) (void)hipHostFree(f->hsc);
 }
 
-// psi = K^-1 b (b, psi: the filter's own node buffers b and x); returns FE_OK,
-// FE_NOT_CONVERGED or an error
+// Tiles as wide as divides the grid best, up to TILE_W.  Planes per tile: each tile
+// stages two planes more than it has, but fewer tiles than 1.5 per CU leave the chip
+// idle and one plane per tile doubles what a tile stages (us per solve at 1 / 2 / 4 /
+// 6 / 8 planes, 24 iterations: 32x32x64 340 294 372 379 393; 64x64x128 591 539 481
+// 469 514; 96^3 706 656 669 568 631; 160x160x320 5503 4900 4694 4655 4585).
+static CgTiling cg_tiling(const FGeo &g)
+{
+    CgTiling t;
+    t.nx = (g.nx + TILE_W) / TILE_W;
+    t.wx = (g.nx + t.nx) / t.nx;
+    t.wy = std::min(RED_THREADS / t.wx, g.ny + 1);
+    t.ny = (g.ny + t.wy) / t.wy;
+    const int64_t cz = (int64_t)t.nx * t.ny * (g.nz + 1) / 400;
+    t.cz = (int)std::min<int64_t>(std::max<int64_t>(2, std::min<int64_t>(cz, 8)), g.nz + 1);
+    t.tiles = t.nx * t.ny * ((g.nz + t.cz) / t.cz);
+    return t;
+}
+
+// psi = K^-1 b (b, psi: the filter's own node buffers b and x; b is overwritten);
+// returns FE_OK, FE_NOT_CONVERGED or an error
 int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
 {
     const FGeo &g = f->g;
-    const dim3 rb(RED_BLOCKS), rt(RED_THREADS);
-    hipLaunchKernelGGL(k_cg_init, rb, rt, 0, st, g, (const double *)f->b, f->x, f->r, f->p,
-                       f->partial);
-    // sc[0] = rz, sc[3] = rr; rr0 kept in sc[4]
-    FE_CHECK_HIP(launch_reduce(f->partial, 1, f->sc + 0, nullptr, false, st));
-    FE_CHECK_HIP(launch_reduce(f->partial + RED_BLOCKS, 1, f->sc + 4, nullptr, false, st));
-    FE_CHECK_HIP(hipMemcpyAsync(f->hsc + 4, f->sc + 4, sizeof(double), hipMemcpyDeviceToHost, st));
-    FE_CHECK_HIP(hipStreamSynchronize(st));
-    const double rr0 = f->hsc[4];
-    f->last_its = 0;
-    if (!(rr0 > 0.0)) return rr0 == 0.0 ? FE_OK : FE_ENAN;
+    const CgTiling t = cg_tiling(g);
+    const int nb = std::min(t.tiles, RED_BLOCKS);
+    const dim3 gb(nb), gt(RED_THREADS);
+    double *ppy = f->partial, *prz = f->partial + RED_BLOCKS, *prr = f->partial + 2 * RED_BLOCKS;
+    const double iE0 = 1.0 / g.E[0];
+    hipLaunchKernelGGL(k_cg_init, gb, gt, 0, st, g, t, iE0, (const double *)f->b, f->x, f->r, prz,
+                       prr);
+    FE_CHECK_HIP(hipGetLastError());
+    // sc[0], sc[1]: rz of the last two iterations; sc[3] = rr, sc[4] = its first value;
+    // sc[5]: alpha of the iteration before
+    FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 4, nullptr, false, st, nb));
+    double *pn = f->p, *po = f->b;
     int cur = 0;
+    f->last_its = 0;
     for (int it = 1; it <= max_its; ++it) {
-        hipLaunchKernelGGL(k_cg_apply, rb, rt, 0, st, g, (const double *)f->p, f->y, f->partial);
-        FE_CHECK_HIP(launch_reduce(f->partial, 1, f->sc + 2, nullptr, false, st));
-        hipLaunchKernelGGL(k_cg_step, rb, rt, 0, st, g, (const double *)f->sc, cur,
-                           (const double *)f->p, (const double *)f->y, f->x, f->r, f->partial);
-        FE_CHECK_HIP(launch_reduce(f->partial, 1, f->sc + (1 - cur), nullptr, false, st));
-        FE_CHECK_HIP(launch_reduce(f->partial + RED_BLOCKS, 1, f->sc + 3, nullptr, false, st));
-        hipLaunchKernelGGL(k_cg_dir, dim3(nblk(f->nn)), dim3(256), 0, st, g, (const double *)f->sc,
-                           cur, (const double *)f->r, f->p);
+        if (it == 1)
+            hipLaunchKernelGGL(k_cg_apply<true>, gb, gt, 0, st, g, t, nb, (const double *)prz, f->sc,
+                               cur, (const double *)f->r, (const double *)po, pn, f->y, ppy);
+        else
+            hipLaunchKernelGGL(k_cg_apply<false>, gb, gt, 0, st, g, t, nb, (const double *)prz,
+                               f->sc, cur, (const double *)f->r, (const double *)po, pn, f->y, ppy);
+        if (it % 2 == 0 || it == max_its)
+            hipLaunchKernelGGL(k_cg_step<true>, gb, gt, 0, st, g, t, nb, iE0, (const double *)ppy,
+                               f->sc, cur, it % 2 == 0, (const double *)po, (const double *)pn,
+                               (const double *)f->y, f->x, f->r, prz, prr);
+        else
+            hipLaunchKernelGGL(k_cg_step<false>, gb, gt, 0, st, g, t, nb, iE0, (const double *)ppy,
+                               f->sc, cur, 0, (const double *)po, (const double *)pn,
+                               (const double *)f->y, f->x, f->r, prz, prr);
         FE_CHECK_HIP(hipGetLastError());
         cur = 1 - cur;
-        f->last_its = it;
+        std::swap(pn, po);
         if (it % 8 == 0 || it == max_its) {
-            FE_CHECK_HIP(hipMemcpyAsync(f->hsc + 3, f->sc + 3, sizeof(double),
+            FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 3, nullptr, false, st, nb));
+            FE_CHECK_HIP(hipMemcpyAsync(f->hsc + 3, f->sc + 3, 2 * sizeof(double),
                                         hipMemcpyDeviceToHost, st));
             FE_CHECK_HIP(hipStreamSynchronize(st));
-            const double rr = f->hsc[3];
+            const double rr = f->hsc[3], rr0 = f->hsc[4];
+            if (rr0 == 0.0) return FE_OK;
+            if (!(rr0 > 0.0)) return FE_ENAN;
+            f->last_its = it;
             if (!std::isfinite(rr)) return FE_ENAN;
             if (rr <= rtol * rtol * rr0) return FE_OK;
         }
