@@ -34,9 +34,6 @@ hipError_t mg_inject_state(const fe_grid &c, const fe_grid &f, const double *fv,
 hipError_t mg_inject_mask(const fe_grid &c, const fe_grid &f, const uint8_t *fv, uint8_t *cv,
                           hipStream_t st);
 template <typename T>
-hipError_t mg_restrict(const fe_grid &c, const fe_grid &f, const T *b, const T *t,
-                       const uint8_t *cmask, T *bc, hipStream_t st);
-template <typename T>
 hipError_t mg_restrict_smooth(const fe_grid &c, const fe_grid &f, const T *b, const T *t,
                               const uint8_t *cmask, T *bc, const T *Dc, T *xc, T omega,
                               bool transpose, hipStream_t st);
@@ -53,8 +50,23 @@ hipError_t mg_stencil_diag(int64_t nn, const double *S, double *D, hipStream_t s
 hipError_t mg_coarse_inverse(int n, int kl, int ku, const double *Lc, const double *Uc,
                              const double *Ud, const int *piv, double *X, hipStream_t st);
 template <typename T>
-hipError_t mg_coarse_apply(int n, int m, const double *X, const int *fidx, const int *pos, const T *b,
-                           T *x, double *P, bool transpose, hipStream_t st);
+hipError_t mg_restrict_coarse(const fe_grid &c, const fe_grid &f, int n, const double *X,
+                              const int *fidx, const T *b, const T *t, double *P, bool transpose,
+                              hipStream_t st);
+template <typename T>
+hipError_t mg_coarse_sum(int nfull, int n, const int *pos, const double *P, T *x, hipStream_t st);
+template <typename T>
+hipError_t mg_sweep_first(int nx, int ny, int nz, const T *S, const T *D, const T *b,
+                          const double *v, T *bout, T *xout, T omega, bool transpose, hipStream_t st);
+template <typename T>
+hipError_t mg_sweep_prolong(const fe_grid &f, const fe_grid &c, const T *S, const T *D, const T *b,
+                            const T *x, const T *xc, const uint8_t *fmask, T *xout, T omega,
+                            bool transpose, hipStream_t st);
+bool mg_sweep_coarse_pays(int nfull, int n);
+template <typename T>
+hipError_t mg_sweep_coarse(const fe_grid &f, const fe_grid &c, const T *S, const T *D, const T *b,
+                           const T *x, int nfull, int n, const int *pos, const double *P,
+                           const uint8_t *fmask, T *xout, T omega, bool transpose, hipStream_t st);
 template <typename T>
 hipError_t mg_stencil_smooth(int nx, int ny, int nz, const T *S, const T *D, const T *b, const T *xin,
                              T *xout, T omega, bool transpose, hipStream_t st);
@@ -582,66 +594,111 @@ static hipError_t op(const MgLevel &L, const T *v, T *out, bool tr, hipStream_t 
 }
 
 template <typename T>
-static int coarse_solve(Mg *mg, const T *b, T *x, bool tr, hipStream_t st)
-{
-    FE_CHECK_HIP(mg_coarse_apply<T>((int)mg->nc, (int)mg->nf, mg->Xinv, mg->dmap, mg->dmap + mg->nc, b,
-                                    x, mg->cpart, tr, st));
-    return FE_OK;
-}
-
-template <typename T>
 static T *altT(MgLevel &L);
 template <>
 double *altT<double>(MgLevel &L) { return L.xa; }
 template <>
 float *altT<float>(MgLevel &L) { return L.xa32; }
 
-// V-cycle from level l on b; x receives the result.  first_done: the first
-// pre-smoothing sweep from x = 0 (x = omega D^{-1} b) has already been applied
-// to x, by the restriction kernel of the level above (or, at the finest level
-// of a mixed-precision cycle, together with the cast of the Krylov vector).
+// x = omega D^{-1} b with b = (float) v (mixed-precision cycles; FP64 has nothing to cast)
+static hipError_t smooth0_cast(MgLevel &L, const double *v, float *b, float *x, float om, bool tr,
+                               hipStream_t st)
+{
+    return mg_smooth0_cast(L.D32, v, b, x, L.nn, om, tr, st);
+}
+static hipError_t smooth0_cast(MgLevel &, const double *, double *, double *, double, bool,
+                               hipStream_t)
+{
+    return hipErrorInvalidValue;
+}
+
+// V-cycle from level l (not the coarsest) on b; x receives the result.
+// first_done: the first pre-smoothing sweep from x = 0 (x = omega D^{-1} b) has
+// already been applied to x, by the restriction kernel of the level above (or, at
+// the finest level of a mixed-precision cycle, together with the cast of the Krylov
+// vector).  v (finest level of a mixed-precision cycle): b is still to be cast from v.
 // A damped block-Jacobi sweep x += omega D^{-1} (b - A x) (transposed when tr)
 // is fused with the element pass on matrix-free levels, and is one kernel on
 // assembled ones, which writes the new iterate to the level's second buffer:
-// the iterate alternates between x and that buffer, and ends in x.
+// the iterate alternates between x and that buffer, and ends in x.  On assembled
+// levels the second sweep also forms the first one's x, and the first sweep after
+// the coarse-grid correction adds that correction.
 template <typename T>
-static int vcycle(Mg *mg, int l, const T *b, T *x, bool tr, hipStream_t st, bool first_done = false)
+static int vcycle(Mg *mg, int l, const T *b, T *x, bool tr, hipStream_t st, bool first_done = false,
+                  const double *v = nullptr)
 {
     MgLevel &L = mg->lev[l];
     const int nl = (int)mg->lev.size();
-    if (l == nl - 1) return coarse_solve<T>(mg, b, x, tr, st);
     const T om = (T)mg->omega;
-    const T *D = blocksT<T>(L);
+    const T *D = blocksT<T>(L), *S = stencilT<T>(L);
     T *t = vecT<T>(L, 2);
     T *cur = x;
+    auto other = [&]() { return cur == x ? altT<T>(L) : x; };
     auto sweep = [&]() -> hipError_t {
         if (L.assembled) {
-            T *nxt = cur == x ? altT<T>(L) : x;
-            const hipError_t e = mg_stencil_smooth<T>(L.grid.nx, L.grid.ny, L.grid.nz, stencilT<T>(L),
-                                                      D, b, cur, nxt, om, tr, st);
+            T *nxt = other();
+            const hipError_t e = mg_stencil_smooth<T>(L.grid.nx, L.grid.ny, L.grid.nz, S, D, b, cur,
+                                                      nxt, om, tr, st);
             cur = nxt;
             return e;
         }
         return launch_elem_smooth<T>(tr, L.geo, stateT<T>(L), cur, L.gamma, L.s, L.nmask, t,
                                      (T *)L.slots, D, b, om, st);
     };
-    if (!first_done) FE_CHECK_HIP(mg_smooth<T>(D, b, nullptr, x, L.nn, om, tr, false, st));
-    for (int it = 1; it < mg->nu1; ++it) FE_CHECK_HIP(sweep());
+    int pre = 1;
+    if (!first_done) {
+        if (L.assembled && mg->nu1 > 1) {
+            T *nxt = other();
+            FE_CHECK_HIP(mg_sweep_first<T>(L.grid.nx, L.grid.ny, L.grid.nz, S, D, b, v,
+                                           v ? const_cast<T *>(b) : nullptr, nxt, om, tr, st));
+            cur = nxt;
+            pre = 2;
+        } else if (v) {
+            FE_CHECK_HIP(smooth0_cast(L, v, const_cast<T *>(b), x, om, tr, st));
+        } else {
+            FE_CHECK_HIP(mg_smooth<T>(D, b, nullptr, x, L.nn, om, tr, false, st));
+        }
+    }
+    for (int it = pre; it < mg->nu1; ++it) FE_CHECK_HIP(sweep());
     MgLevel &C = mg->lev[l + 1];
     FE_CHECK_HIP(op<T>(L, cur, t, tr, st));
     T *bc = vecT<T>(C, 0), *xc = vecT<T>(C, 1);
-    // below the coarse level's first sweep is fused into the restriction,
-    // except where that level is the directly solved coarsest one
-    const bool fuse = l + 1 < nl - 1;
-    if (fuse)
+    int post = 0;
+    if (l + 1 < nl - 1) {
+        // the coarse level's first sweep is fused into the restriction
         FE_CHECK_HIP(mg_restrict_smooth<T>(C.grid, L.grid, b, t, C.nmask, bc, blocksT<T>(C), xc, om,
                                            tr, st));
-    else
-        FE_CHECK_HIP(mg_restrict<T>(C.grid, L.grid, b, t, C.nmask, bc, st));
-    int rc = vcycle<T>(mg, l + 1, bc, xc, tr, st, fuse);
-    if (rc) return rc;
-    FE_CHECK_HIP(mg_prolong_add<T>(L.grid, C.grid, xc, L.nmask, cur, st));
-    for (int it = 0; it < mg->nu2; ++it) FE_CHECK_HIP(sweep());
+        int rc = vcycle<T>(mg, l + 1, bc, xc, tr, st, true);
+        if (rc) return rc;
+    } else {
+        // directly solved coarsest level: x_c = A^{-1} R (b - t)
+        const int nc = (int)mg->nc, nf = (int)mg->nf;
+        const int *pos = mg->dmap + mg->nc;
+        if (nf > 0)
+            FE_CHECK_HIP(mg_restrict_coarse<T>(C.grid, L.grid, nf, mg->Xinv, mg->dmap, b, t,
+                                               mg->cpart, tr, st));
+        if (L.assembled && mg->nu2 > 0 && mg_sweep_coarse_pays(nc, nf)) {
+            T *nxt = other();
+            FE_CHECK_HIP(mg_sweep_coarse<T>(L.grid, C.grid, S, D, b, cur, nc, nf, pos, mg->cpart,
+                                            L.nmask, nxt, om, tr, st));
+            cur = nxt;
+            post = 1;
+        } else {
+            FE_CHECK_HIP(mg_coarse_sum<T>(nc, nf, pos, mg->cpart, xc, st));
+        }
+    }
+    if (post == 0) {
+        if (L.assembled && mg->nu2 > 0) {
+            T *nxt = other();
+            FE_CHECK_HIP(mg_sweep_prolong<T>(L.grid, C.grid, S, D, b, cur, xc, L.nmask, nxt, om, tr,
+                                             st));
+            cur = nxt;
+            post = 1;
+        } else {
+            FE_CHECK_HIP(mg_prolong_add<T>(L.grid, C.grid, xc, L.nmask, cur, st));
+        }
+    }
+    for (int it = post; it < mg->nu2; ++it) FE_CHECK_HIP(sweep());
     if (cur != x) FE_CHECK_HIP(mg_copy<T>(cur, x, L.ndof, st));
     return FE_OK;
 }
@@ -653,9 +710,7 @@ int mg_apply64(Mg *mg, const double *v, double *z, bool tr, hipStream_t st)
 
 int mg_apply32(Mg *mg, const double *v, float *z, bool tr, hipStream_t st)
 {
-    MgLevel &L0 = mg->lev[0];
-    FE_CHECK_HIP(mg_smooth0_cast(L0.D32, v, L0.b32, z, L0.nn, (float)mg->omega, tr, st));
-    return vcycle<float>(mg, 0, L0.b32, z, tr, st, true);
+    return vcycle<float>(mg, 0, mg->lev[0].b32, z, tr, st, false, v);
 }
 
 }  // namespace fe

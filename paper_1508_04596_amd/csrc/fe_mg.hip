@@ -15,6 +15,20 @@
 namespace fe {
 namespace {
 
+// What a fused sweep forms its iterate from (k_stencil_sweep).
+template <typename T>
+struct SweepIn {
+    const T *x = nullptr;            // SW_PROLONG, SW_COARSE: the iterate before the correction
+    const uint8_t *fmask = nullptr;  // prescribed bits of the level
+    int ncx = 0, ncy = 0;            // coarse grid
+    const T *xc = nullptr;           // SW_PROLONG: coarse correction
+    int nfull = 0, n = 0, nc = 0;    // SW_COARSE: coarsest DOFs, free ones, partials per row
+    const int *pos = nullptr;        // full -> free index or -1
+    const double *P = nullptr;       // row partials
+    const double *v = nullptr;       // SW_FIRST: right-hand side in FP64 (or b)
+    T *bout = nullptr;               // its copy in T
+};
+
 inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 // coarse element = mean of its children (design and source): 8, or fewer where
@@ -59,25 +73,14 @@ __global__ void k_inject(int ncx, int ncy, int ncz, int nfx, int nfy, int nfz,
     for (int q = 0; q < NV; ++q) c[NV * n + q] = (Tc)f[NV * fn + q];
 }
 
-// b_c = R (b - t) on unprescribed coarse DOFs, 0 on prescribed ones; one
-// thread per coarse DOF.  The 27 fine neighbours are unrolled with clamped
-// addresses and a select for those outside the grid, so that their loads are
-// in flight together (a loop that skips them issues one neighbour at a time);
-// the sum keeps the dz, dy, dx order.
+// (R (b - t)) at field f of coarse node (I, J, K).  The 27 fine neighbours are
+// unrolled with clamped addresses and a select for those outside the grid, so
+// that their loads are in flight together (a loop that skips them issues one
+// neighbour at a time); the sum keeps the dz, dy, dx order.
 template <typename T>
-__device__ __forceinline__ void restrict_dofs(int ncx, int ncy, int ncz, int nfx, int nfy, int nfz,
-                                              const T *__restrict__ b, const T *__restrict__ t,
-                                              const uint8_t *__restrict__ cmask, T *__restrict__ bc,
-                                              unsigned blk)
+__device__ __forceinline__ T restrict_dof(int I, int J, int K, int f, int nfx, int nfy, int nfz,
+                                          const T *__restrict__ b, const T *__restrict__ t)
 {
-    const int64_t nn = (int64_t)(ncx + 1) * (ncy + 1) * (ncz + 1);
-    const int64_t q = (int64_t)blk * blockDim.x + threadIdx.x;
-    if (q >= NF * nn) return;
-    const int64_t n = q / NF;
-    const int f = (int)(q - NF * n);
-    const int I = (int)(n % (ncx + 1));
-    const int64_t r = n / (ncx + 1);
-    const int J = (int)(r % (ncy + 1)), K = (int)(r / (ncy + 1));
     T acc = T(0);
 #pragma unroll
     for (int dz = -1; dz <= 1; ++dz) {
@@ -103,24 +106,34 @@ __device__ __forceinline__ void restrict_dofs(int ncx, int ncy, int ncz, int nfx
             }
         }
     }
-    bc[q] = ((cmask[n] >> f) & 1) ? T(0) : acc;
+    return acc;
 }
 
+// b_c = R (b - t) on unprescribed coarse DOFs, 0 on prescribed ones; one
+// thread per coarse DOF.
 template <typename T>
-__global__ __launch_bounds__(256) void k_restrict(int ncx, int ncy, int ncz, int nfx, int nfy,
-                                                  int nfz, const T *__restrict__ b,
-                                                  const T *__restrict__ t,
-                                                  const uint8_t *__restrict__ cmask,
-                                                  T *__restrict__ bc)
+__device__ __forceinline__ void restrict_dofs(int ncx, int ncy, int ncz, int nfx, int nfy, int nfz,
+                                              const T *__restrict__ b, const T *__restrict__ t,
+                                              const uint8_t *__restrict__ cmask, T *__restrict__ bc,
+                                              unsigned blk)
 {
-    restrict_dofs<T>(ncx, ncy, ncz, nfx, nfy, nfz, b, t, cmask, bc, blockIdx.x);
+    const int64_t nn = (int64_t)(ncx + 1) * (ncy + 1) * (ncz + 1);
+    const int64_t q = (int64_t)blk * blockDim.x + threadIdx.x;
+    if (q >= NF * nn) return;
+    const int64_t n = q / NF;
+    const int f = (int)(q - NF * n);
+    const int I = (int)(n % (ncx + 1));
+    const int64_t r = n / (ncx + 1);
+    const int J = (int)(r % (ncy + 1)), K = (int)(r / (ncy + 1));
+    const T acc = restrict_dof<T>(I, J, K, f, nfx, nfy, nfz, b, t);
+    bc[q] = ((cmask[n] >> f) & 1) ? T(0) : acc;
 }
 
 // The restriction above fused with the first smoothing sweep of the coarse
 // level, which starts from x_c = 0: x_c = omega D_c^{-1} b_c (D_c^{-T} when
 // TR).  A workgroup of 255 threads covers the 5 DOFs of 51 coarse nodes; b_c
 // of a node reaches its other four threads through LDS.  Both results are
-// bitwise those of k_restrict followed by k_smooth (same terms, same order).
+// bitwise those of the restriction followed by k_smooth (same terms, same order).
 template <typename T, bool TR>
 __device__ __forceinline__ void restrict_smooth_nodes(int ncx, int ncy, int ncz, int nfx, int nfy,
                                                       int nfz, const T *__restrict__ b,
@@ -140,31 +153,7 @@ __device__ __forceinline__ void restrict_smooth_nodes(int ncx, int ncy, int ncz,
         const int I = (int)(n % (ncx + 1));
         const int64_t r = n / (ncx + 1);
         const int J = (int)(r % (ncy + 1)), K = (int)(r / (ncy + 1));
-        T acc = T(0);
-#pragma unroll
-        for (int dz = -1; dz <= 1; ++dz) {
-            const int k = 2 * K + dz;
-            const bool inz = k >= 0 && k <= nfz;
-            const int kc = k < 0 ? 0 : (k > nfz ? nfz : k);
-            const T wz = dz == 0 ? T(1) : T(0.5);
-#pragma unroll
-            for (int dy = -1; dy <= 1; ++dy) {
-                const int j = 2 * J + dy;
-                const bool iny = j >= 0 && j <= nfy;
-                const int jc = j < 0 ? 0 : (j > nfy ? nfy : j);
-                const T wy = dy == 0 ? T(1) : T(0.5);
-#pragma unroll
-                for (int dx = -1; dx <= 1; ++dx) {
-                    const int i = 2 * I + dx;
-                    const bool in = inz && iny && i >= 0 && i <= nfx;
-                    const int ic = i < 0 ? 0 : (i > nfx ? nfx : i);
-                    const T w = (dx == 0 ? T(1) : T(0.5)) * wy * wz;
-                    const int64_t fn = ic + (int64_t)(nfx + 1) * (jc + (int64_t)(nfy + 1) * kc);
-                    const T v = w * (b[NF * fn + f] - (t ? t[NF * fn + f] : T(0)));
-                    acc += in ? v : T(0);
-                }
-            }
-        }
+        const T acc = restrict_dof<T>(I, J, K, f, nfx, nfy, nfz, b, t);
         val = ((cmask[n] >> f) & 1) ? T(0) : acc;
         bc[NF * n + f] = val;
     }
@@ -398,6 +387,173 @@ __global__ __launch_bounds__(576) void k_stencil_smooth(int nx, int ny, int nz, 
     stencil_smooth_nodes<T, TR>(nx, ny, nz, S, D, b, xin, xout, omega, blockIdx.x);
 }
 
+// A sweep that forms its iterate on the way.  The stencil reads the iterate at the 9
+// runs of 34 consecutive nodes around a workgroup's 32; here the workgroup computes
+// them into LDS, with the stencil entries already under way, instead of reading what a
+// launch before wrote:
+//   SW_FIRST    x = omega D^{-1} b, the first sweep from x = 0; with in.v, b is the
+//               FP64 Krylov vector, kept in FP32 in in.bout
+//   SW_PROLONG  x = in.x + P in.xc on unprescribed DOFs
+//   SW_COARSE   the same, x_c summed from the coarsest level's row partials
+// The values are those of k_smooth0_cast / k_smooth, k_coarse_apply_sum and
+// k_prolong_add.  A small level's launch costs 3 to 6 us whatever it does; these save
+// one (SW_COARSE: two) each for 2 to 5 us of gathers.  With the gap between launches,
+// V-cycle of 3 levels, kernels alone: FP32 16^3 first sweep 3.6 + 7.0 -> 10.2 us, post
+// sweep 3.4 + 7.0 -> 9.1, above a 4^3 coarsest level 2.6 + 3.4 + 5.6 -> 8.7; FP64
+// 16x16x32 post sweep 4.1 + 15 -> 17.7, above 4x4x8 2.6 + 3.5 + 9.2 -> 12.6.  13
+// launches -> 9.  What bounds them is the stencil's read (16x16x32 in FP64: 51 MB) and,
+// below 10^4 nodes, the chain of gather, stencil, sum and block product.
+enum { SW_FIRST = 0, SW_PROLONG = 1, SW_COARSE = 2 };
+
+template <typename T, bool TR, int MODE>
+__global__ __launch_bounds__(576) void k_stencil_sweep(int nx, int ny, int nz,
+                                                       const T *__restrict__ S,
+                                                       const T *__restrict__ D,
+                                                       const T *__restrict__ b, SweepIn<T> in,
+                                                       T *__restrict__ xout, T omega)
+{
+    constexpr int SN = STENCIL_SMOOTH_NODES, RUN = (SN + 2) * NF;
+    // FP32 issues its stencil loads ahead of the gathers; in FP64 they would take 90
+    // registers more, which leaves one workgroup per CU
+    constexpr bool AHEAD = sizeof(T) == 4;
+    extern __shared__ char coarse_mem[];  // SW_COARSE: the coarsest level's x
+    __shared__ T sx[9 * RUN];
+    __shared__ T part[9][NF][SN];
+    __shared__ T sD[SN * 25];
+    const int sxy = (nx + 1) * (ny + 1), nn = sxy * (nz + 1);  // (675 nn entries fit the device)
+    const int tid = (int)threadIdx.x, lane = tid & 63, p = tid >> 6;
+    const int ln = lane & (SN - 1), half = lane >> 5;
+    const int g0 = half ? 3 : 0, ng = half ? NF - 3 : 3;
+    const int n0 = (int)blockIdx.x * SN;
+    const int N = n0 + ln;
+    const bool live = N < nn;
+    const int Nc = live ? N : nn - 1;
+    const int K = Nc / sxy, r = Nc - K * sxy, J = r / (nx + 1), I = r - J * (nx + 1);
+    const int j = J + p % 3 - 1, k = K + p / 3 - 1;
+    const bool injk = j >= 0 && j <= ny && k >= 0 && k <= nz;
+    // offsets 3p .. 3p + 2, row fields g0 .. g0 + ng - 1 of this lane's node
+    bool inc[3];
+    int M3[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int i = I + c - 1;
+        inc[c] = live && injk && i >= 0 && i <= nx;
+        M3[c] = TR && inc[c] ? Nc + c - 1 + (p % 3 - 1) * (nx + 1) + (p / 3 - 1) * sxy : Nc;
+    }
+    auto entry = [&](int gg, int c, int f) {
+        const int d = 3 * p + c, g = g0 + gg;
+        return S[(TR ? (26 - d) * 25 + f * NF + g : d * 25 + g * NF + f) * (int64_t)nn + M3[c]];
+    };
+    T a[3][3 * NF];
+    if (AHEAD) {
+#pragma unroll
+        for (int gg = 0; gg < 3; ++gg)
+            if (gg < ng)
+#pragma unroll
+                for (int q = 0; q < 3 * NF; ++q) a[gg][q] = entry(gg, q / NF, q % NF);
+    }
+    // the workgroup's nodal blocks, coalesced (entries past nn repeat the last)
+    {
+        const int cnt = min(nn - n0, SN) * 25;
+        const T *src = D + (int64_t)n0 * 25;
+#pragma unroll
+        for (int m = 0; m < (SN * 25 + 575) / 576; ++m) {
+            const int q = tid + 576 * m;
+            if (q < SN * 25) sD[q] = src[q < cnt ? q : cnt - 1];
+        }
+    }
+    T *xco = reinterpret_cast<T *>(coarse_mem);
+    if (MODE == SW_COARSE) {
+        for (int q = tid; q < in.nfull; q += 576) {
+            const int row = in.pos[q];
+            const double *P = in.P + (row < 0 ? 0 : row);
+            double acc = 0.0;
+#pragma unroll 8
+            for (int c = 0; c < in.nc; ++c) acc += P[c * in.n];
+            xco[q] = row < 0 ? T(0) : (T)acc;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int m = 0; m < (9 * RUN + 575) / 576; ++m) {
+        const int q = tid + 576 * m;
+        if (q >= 9 * RUN) break;
+        const int run = q / RUN, e = q - run * RUN, en = e / NF, f = e - NF * en;
+        const int M0 = n0 - 1 + en + (run % 3 - 1) * (nx + 1) + (run / 3 - 1) * sxy;
+        const int M = min(max(M0, 0), nn - 1);  // (not read by any lane where clamped)
+        T x;
+        if (MODE == SW_FIRST) {
+            T acc = T(0), own = T(0);
+#pragma unroll
+            for (int c = 0; c < NF; ++c) {
+                const T bv = in.v ? (T)in.v[NF * M + c] : b[NF * M + c];
+                acc += D[M * 25 + (TR ? c * NF + f : f * NF + c)] * bv;
+                if (c == f) own = bv;
+            }
+            x = omega * acc;
+            if (in.bout && run == 4 && M0 >= n0 && M0 < n0 + SN && M0 < nn) in.bout[NF * M + f] = own;
+        } else {
+            const int fk = M / sxy, fr = M - fk * sxy, fj = fr / (nx + 1), fi = fr - fj * (nx + 1);
+            const int oi = fi & 1, oj = fj & 1, ok = fk & 1;
+            const T wi = oi ? T(0.5) : T(1), wj = oj ? T(0.5) : T(1), wk = ok ? T(0.5) : T(1);
+            const T *xc = MODE == SW_COARSE ? xco : in.xc;
+            T acc = T(0);
+#pragma unroll
+            for (int cz = 0; cz < 2; ++cz)
+#pragma unroll
+                for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+                    for (int cx = 0; cx < 2; ++cx) {
+                        const bool use = (cz <= ok) && (cy <= oj) && (cx <= oi);
+                        const int cn = ((fi >> 1) + cx * oi) +
+                                       (in.ncx + 1) * (((fj >> 1) + cy * oj) +
+                                                       (in.ncy + 1) * ((fk >> 1) + cz * ok));
+                        const T v = xc[NF * cn + f];
+                        acc += use ? v : T(0);
+                    }
+            const int mk = in.fmask[M];
+            const T xq = in.x[NF * M + f];
+            x = ((mk >> f) & 1) ? xq : xq + wi * wj * wk * acc;
+        }
+        sx[q] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int gg = 0; gg < 3; ++gg) {
+        if (gg < ng) {
+            T acc = T(0);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    const T t = (AHEAD ? a[gg][c * NF + f] : entry(gg, c, f)) *
+                                sx[p * RUN + (ln + c) * NF + f];
+                    acc += inc[c] ? t : T(0);
+                }
+            part[p][g0 + gg][ln] = acc;
+        }
+    }
+    __syncthreads();
+    if (p == 0 && half == 0 && live) {
+        const T *Dn = sD + ln * 25;
+        T rr[NF];
+#pragma unroll
+        for (int g = 0; g < NF; ++g) {
+            T sum = part[0][g][ln];
+#pragma unroll
+            for (int w = 1; w < 9; ++w) sum += part[w][g][ln];
+            rr[g] = (MODE == SW_FIRST && in.v ? (T)in.v[NF * N + g] : b[NF * N + g]) - sum;
+        }
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+            T acc = T(0);
+#pragma unroll
+            for (int c = 0; c < NF; ++c) acc += (TR ? Dn[c * NF + q] : Dn[q * NF + c]) * rr[c];
+            xout[NF * N + q] = sx[4 * RUN + (ln + 1) * NF + q] + omega * acc;
+        }
+    }
+}
+
 // The first sweep from x = 0 of a mixed-precision V-cycle, reading the FP64
 // Krylov vector: b32 = (float) v and x = omega D^{-1} b32 (D^{-T} when TR) per
 // node -- bitwise k_cast followed by k_smooth<float, TR, false>.
@@ -625,61 +781,87 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse(int n, int kl, int w, c
 // products are summed through LDS).
 constexpr int CA_B = 64;
 
-template <typename T, bool TR>
+template <typename T>
 __device__ __forceinline__ void coarse_apply_tile(int n, const double *__restrict__ X,
                                                   const int *__restrict__ fidx,
                                                   const T *__restrict__ b, double *__restrict__ P,
                                                   unsigned bx, unsigned by)
 {
     __shared__ double tile[4][CA_B + 1];
-    __shared__ double prod[CA_B][CA_B + 1];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int i0 = bx * CA_B, j0 = by * CA_B;
+    const int i = bx * CA_B + lane, j0 = by * CA_B;
+    const int ic = i < n ? i : n - 1;
+    double acc = 0.0;
+#pragma unroll
+    for (int m = 0; m < CA_B / 4; ++m) {
+        const int j = j0 + q + 4 * m;
+        const int jc = j < n ? j : n - 1;
+        const double t = X[(int64_t)jc * n + ic] * (double)b[fidx[jc]];
+        acc += j < n ? t : 0.0;
+    }
+    tile[q][lane] = acc;
+    __syncthreads();
+    if (q == 0 && i < n)
+        P[(int64_t)by * n + i] = ((tile[0][lane] + tile[1][lane]) + tile[2][lane]) + tile[3][lane];
+}
+
+// Pass 1 of a single problem, with the restriction to the coarsest level in it (the
+// batched one above reads b_c): each workgroup restricts
+// the 64 entries of b_c that its tile multiplies (nc workgroups repeat an entry;
+// it saves a launch), the tile's loads already under way.
+template <typename T, bool TR>
+__global__ __launch_bounds__(256) void k_restrict_coarse_part(int n, const double *__restrict__ X,
+                                                              const int *__restrict__ fidx, int ncx,
+                                                              int ncy, int nfx, int nfy, int nfz,
+                                                              const T *__restrict__ b,
+                                                              const T *__restrict__ t,
+                                                              double *__restrict__ P)
+{
+    __shared__ double tile[4][CA_B];
+    __shared__ double prod[TR ? CA_B : 1][CA_B + 1];
+    __shared__ double sb[CA_B];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int i0 = blockIdx.x * CA_B, j0 = blockIdx.y * CA_B;
+    double xv[CA_B / 4];
+#pragma unroll
+    for (int m = 0; m < CA_B / 4; ++m) {
+        const int i = min(TR ? i0 + q + 4 * m : i0 + lane, n - 1);
+        const int j = min(TR ? j0 + lane : j0 + q + 4 * m, n - 1);
+        xv[m] = X[TR ? (int64_t)i * n + j : (int64_t)j * n + i];
+    }
+    if (threadIdx.x < CA_B) {
+        const int j = j0 + (int)threadIdx.x;
+        const int d = fidx[j < n ? j : n - 1], node = d / NF, f = d - NF * node;
+        const int I = node % (ncx + 1), r = node / (ncx + 1), J = r % (ncy + 1), K = r / (ncy + 1);
+        const T v = restrict_dof<T>(I, J, K, f, nfx, nfy, nfz, b, t);
+        sb[threadIdx.x] = j < n ? (double)v : 0.0;
+    }
+    __syncthreads();
     if (!TR) {
-        const int i = i0 + lane;
-        const int ic = i < n ? i : n - 1;
         double acc = 0.0;
 #pragma unroll
-        for (int m = 0; m < CA_B / 4; ++m) {
-            const int j = j0 + q + 4 * m;
-            const int jc = j < n ? j : n - 1;
-            const double t = X[(int64_t)jc * n + ic] * (double)b[fidx[jc]];
-            acc += j < n ? t : 0.0;
-        }
+        for (int m = 0; m < CA_B / 4; ++m) acc += xv[m] * sb[q + 4 * m];
         tile[q][lane] = acc;
         __syncthreads();
+        const int i = i0 + lane;
         if (q == 0 && i < n)
-            P[(int64_t)by * n + i] = ((tile[0][lane] + tile[1][lane]) + tile[2][lane]) + tile[3][lane];
+            P[(int64_t)blockIdx.y * n + i] =
+                ((tile[0][lane] + tile[1][lane]) + tile[2][lane]) + tile[3][lane];
     } else {
-        const int j = j0 + lane;
-        const int jc = j < n ? j : n - 1;
-        const double bj = j < n ? (double)b[fidx[jc]] : 0.0;
 #pragma unroll
-        for (int m = 0; m < CA_B / 4; ++m) {
-            const int r = q + 4 * m;
-            const int i = i0 + r;
-            const int ic = i < n ? i : n - 1;
-            prod[r][lane] = X[(int64_t)ic * n + jc] * bj;
-        }
+        for (int m = 0; m < CA_B / 4; ++m) prod[TR ? q + 4 * m : 0][lane] = xv[m] * sb[lane];
         __syncthreads();
-        if (threadIdx.x < CA_B) {
-            const int i = i0 + threadIdx.x;
+        const int i = i0 + (int)threadIdx.x;
+        if (threadIdx.x < CA_B && i < n) {
             double acc = 0.0;
-            for (int l = 0; l < CA_B; ++l) acc += prod[threadIdx.x][l];
-            if (i < n) P[(int64_t)by * n + i] = acc;
+            for (int l = 0; l < CA_B; ++l) acc += prod[TR ? threadIdx.x : 0][l];
+            P[(int64_t)blockIdx.y * n + i] = acc;
         }
     }
 }
 
-template <typename T, bool TR>
-__global__ __launch_bounds__(256) void k_coarse_apply_part(int n, const double *__restrict__ X,
-                                                           const int *__restrict__ fidx,
-                                                           const T *__restrict__ b, double *__restrict__ P)
-{
-    coarse_apply_tile<T, TR>(n, X, fidx, b, P, blockIdx.x, blockIdx.y);
-}
-
-// Pass 2 over the full vector (nfull DOFs; pos: full -> free index, -1 when prescribed).
+// Pass 2 over the full vector (nfull DOFs; pos: full -> free index, -1 when prescribed;
+// b NULL: 0 on prescribed DOFs, as the restriction leaves them).
 template <typename T>
 __device__ __forceinline__ void coarse_apply_rows(int nfull, int n, int nc, const int *__restrict__ pos,
                                                   const double *__restrict__ P,
@@ -690,7 +872,7 @@ __device__ __forceinline__ void coarse_apply_rows(int nfull, int n, int nc, cons
     if (i >= nfull) return;
     const int r = pos[i];
     if (r < 0) {
-        x[i] = b[i];
+        x[i] = b ? b[i] : T(0);
         return;
     }
     double acc = 0.0;
@@ -813,8 +995,8 @@ __global__ __launch_bounds__(256) void kb_coarse_part(const BCoarse<T> *__restri
     const int e = batch_entry(off, n);
     const BCoarse<T> &a = tab[e];
     const unsigned lb = blockIdx.x - (unsigned)off[e];
-    coarse_apply_tile<T, false>(a.n, a.X, a.fidx, a.b, a.P, lb % (unsigned)a.nt,
-                                lb / (unsigned)a.nt);
+    coarse_apply_tile<T>(a.n, a.X, a.fidx, a.b, a.P, lb % (unsigned)a.nt,
+                         lb / (unsigned)a.nt);
 }
 
 template <typename T>
@@ -870,16 +1052,6 @@ hipError_t mg_inject_mask(const fe_grid &c, const fe_grid &f, const uint8_t *fv,
     const int64_t n = (int64_t)(c.nx + 1) * (c.ny + 1) * (c.nz + 1);
     hipLaunchKernelGGL((k_inject<uint8_t, uint8_t, 1>), dim3(nblk(n)), dim3(256), 0, st, c.nx, c.ny,
                        c.nz, f.nx, f.ny, f.nz, fv, cv);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t mg_restrict(const fe_grid &c, const fe_grid &f, const T *b, const T *t,
-                       const uint8_t *cmask, T *bc, hipStream_t st)
-{
-    const int64_t n = (int64_t)(c.nx + 1) * (c.ny + 1) * (c.nz + 1);
-    hipLaunchKernelGGL(k_restrict<T>, dim3(nblk(NF * n)), dim3(256), 0, st, c.nx, c.ny, c.nz, f.nx,
-                       f.ny, f.nz, b, t, cmask, bc);
     return hipGetLastError();
 }
 
@@ -959,22 +1131,99 @@ hipError_t mg_coarse_inverse(int n, int kl, int ku, const double *Lc, const doub
     return hipGetLastError();
 }
 
-// nfull DOFs, m of them free; X: m x m; P: work space of ceil(m / 64) * m doubles
+// First pass on the coarsest level: row partials P (ceil(n / 64) of n each) of
+// A^{-1} R (b - t) (A^{-T} when transpose); n > 0 free DOFs, X: n x n.
 template <typename T>
-hipError_t mg_coarse_apply(int nfull, int m, const double *X, const int *fidx, const int *pos, const T *b,
-                           T *x, double *P, bool transpose, hipStream_t st)
+hipError_t mg_restrict_coarse(const fe_grid &c, const fe_grid &f, int n, const double *X,
+                              const int *fidx, const T *b, const T *t, double *P, bool transpose,
+                              hipStream_t st)
 {
-    const int nc = (m + CA_B - 1) / CA_B;
-    const dim3 grid((unsigned)nc, (unsigned)nc);
-    if (m > 0) {
-        if (transpose)
-            hipLaunchKernelGGL((k_coarse_apply_part<T, true>), grid, dim3(256), 0, st, m, X, fidx, b, P);
-        else
-            hipLaunchKernelGGL((k_coarse_apply_part<T, false>), grid, dim3(256), 0, st, m, X, fidx, b, P);
-    }
-    hipLaunchKernelGGL(k_coarse_apply_sum<T>, dim3((unsigned)((nfull + 255) / 256)), dim3(256), 0, st, nfull,
-                       m, nc, pos, (const double *)P, b, x);
+    const unsigned nc = (unsigned)((n + CA_B - 1) / CA_B);
+    if (transpose)
+        hipLaunchKernelGGL((k_restrict_coarse_part<T, true>), dim3(nc, nc), dim3(256), 0, st, n, X,
+                           fidx, c.nx, c.ny, f.nx, f.ny, f.nz, b, t, P);
+    else
+        hipLaunchKernelGGL((k_restrict_coarse_part<T, false>), dim3(nc, nc), dim3(256), 0, st, n, X,
+                           fidx, c.nx, c.ny, f.nx, f.ny, f.nz, b, t, P);
     return hipGetLastError();
+}
+
+// Second pass: x (nfull DOFs) from the row partials.
+template <typename T>
+hipError_t mg_coarse_sum(int nfull, int n, const int *pos, const double *P, T *x, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_coarse_apply_sum<T>, dim3((unsigned)((nfull + 255) / 256)), dim3(256), 0, st,
+                       nfull, n, (n + CA_B - 1) / CA_B, pos, P, (const T *)nullptr, x);
+    return hipGetLastError();
+}
+
+template <typename T, int MODE>
+static hipError_t sweep_launch(int nx, int ny, int nz, const T *S, const T *D, const T *b,
+                               const SweepIn<T> &in, T *xout, T omega, bool transpose,
+                               hipStream_t st)
+{
+    const int64_t n = (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
+    const dim3 grid(nblk(n, STENCIL_SMOOTH_NODES)), block(576);
+    const unsigned lds = MODE == SW_COARSE ? (unsigned)(in.nfull * sizeof(T)) : 0u;
+    if (transpose)
+        hipLaunchKernelGGL((k_stencil_sweep<T, true, MODE>), grid, block, lds, st, nx, ny, nz, S, D,
+                           b, in, xout, omega);
+    else
+        hipLaunchKernelGGL((k_stencil_sweep<T, false, MODE>), grid, block, lds, st, nx, ny, nz, S, D,
+                           b, in, xout, omega);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t mg_sweep_first(int nx, int ny, int nz, const T *S, const T *D, const T *b,
+                          const double *v, T *bout, T *xout, T omega, bool transpose, hipStream_t st)
+{
+    SweepIn<T> in;
+    in.v = v;
+    in.bout = bout;
+    return sweep_launch<T, SW_FIRST>(nx, ny, nz, S, D, b, in, xout, omega, transpose, st);
+}
+
+template <typename T>
+hipError_t mg_sweep_prolong(const fe_grid &f, const fe_grid &c, const T *S, const T *D, const T *b,
+                            const T *x, const T *xc, const uint8_t *fmask, T *xout, T omega,
+                            bool transpose, hipStream_t st)
+{
+    SweepIn<T> in;
+    in.x = x;
+    in.xc = xc;
+    in.fmask = fmask;
+    in.ncx = c.nx;
+    in.ncy = c.ny;
+    return sweep_launch<T, SW_PROLONG>(f.nx, f.ny, f.nz, S, D, b, in, xout, omega, transpose, st);
+}
+
+// Every workgroup sums the coarsest level's partials itself, which pays while that is
+// at most SUMS_PER_THREAD loads per thread: 4^3 (5 loads) 5 us saved, 4x4x8 (18) 2.7 us,
+// the next size up (5x5x10: 55) costs more than the two launches.  Its x is held in LDS:
+// the coarsest level has at most 2400 DOFs (19 KB).
+constexpr int SUMS_PER_THREAD = 20;
+bool mg_sweep_coarse_pays(int nfull, int n)
+{
+    return (int64_t)nfull * ((n + CA_B - 1) / CA_B) <= 576ll * SUMS_PER_THREAD;
+}
+
+template <typename T>
+hipError_t mg_sweep_coarse(const fe_grid &f, const fe_grid &c, const T *S, const T *D, const T *b,
+                           const T *x, int nfull, int n, const int *pos, const double *P,
+                           const uint8_t *fmask, T *xout, T omega, bool transpose, hipStream_t st)
+{
+    SweepIn<T> in;
+    in.x = x;
+    in.fmask = fmask;
+    in.ncx = c.nx;
+    in.ncy = c.ny;
+    in.nfull = nfull;
+    in.n = n;
+    in.nc = (n + CA_B - 1) / CA_B;
+    in.pos = pos;
+    in.P = P;
+    return sweep_launch<T, SW_COARSE>(f.nx, f.ny, f.nz, S, D, b, in, xout, omega, transpose, st);
 }
 
 template <typename T>
@@ -1011,9 +1260,6 @@ hipError_t mg_copy(const T *a, T *b, int64_t n, hipStream_t st)
 }
 
 #define FE_MG_INST(T)                                                                          \
-    template hipError_t mg_restrict<T>(const fe_grid &, const fe_grid &, const T *, const T *,      \
-                                       const uint8_t *, T *,                                      \
-                                       hipStream_t);                                           \
     template hipError_t mg_restrict_smooth<T>(const fe_grid &, const fe_grid &, const T *,       \
                                               const T *, const uint8_t *, T *, const T *, T *, T,  \
                                               bool, hipStream_t);                                 \
@@ -1024,8 +1270,19 @@ hipError_t mg_copy(const T *a, T *b, int64_t n, hipStream_t st)
                                      hipStream_t);                                             \
     template hipError_t mg_stencil_apply<T>(int, int, int, const T *, const T *, T *, bool,      \
                                             hipStream_t);                                      \
-    template hipError_t mg_coarse_apply<T>(int, int, const double *, const int *, const int *,    \
-                                           const T *, T *, double *, bool, hipStream_t);        \
+    template hipError_t mg_restrict_coarse<T>(const fe_grid &, const fe_grid &, int,              \
+                                              const double *, const int *, const T *, const T *,  \
+                                              double *, bool, hipStream_t);                       \
+    template hipError_t mg_coarse_sum<T>(int, int, const int *, const double *, T *, hipStream_t); \
+    template hipError_t mg_sweep_first<T>(int, int, int, const T *, const T *, const T *,         \
+                                          const double *, T *, T *, T, bool, hipStream_t);        \
+    template hipError_t mg_sweep_prolong<T>(const fe_grid &, const fe_grid &, const T *,          \
+                                            const T *, const T *, const T *, const T *,           \
+                                            const uint8_t *, T *, T, bool, hipStream_t);          \
+    template hipError_t mg_sweep_coarse<T>(const fe_grid &, const fe_grid &, const T *, const T *, \
+                                           const T *, const T *, int, int, const int *,           \
+                                           const double *, const uint8_t *, T *, T, bool,         \
+                                           hipStream_t);                                          \
     template hipError_t mg_stencil_smooth<T>(int, int, int, const T *, const T *, const T *,      \
                                              const T *, T *, T, bool, hipStream_t);              \
     template hipError_t mg_copy<T>(const T *, T *, int64_t, hipStream_t);
