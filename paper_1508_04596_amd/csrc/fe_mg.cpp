@@ -428,11 +428,11 @@ static int band_lu(Mg *mg)
         }
         for (int64_t i = iend + 1; i <= k + kl; ++i) Lc[k * kl + (i - k - 1)] = 0.0;
     }
-    // U by columns: Uc[k w + t] = U(k - w + t, k), and its diagonal
+    // U by columns: Uc[k w + q] = U(k - 1 - q, k), and its diagonal
     for (int64_t k = 0; k < n; ++k) {
-        for (int64_t t = 0; t < w; ++t) {
-            const int64_t r = k - w + t;
-            Uc[k * w + t] = r >= 0 ? A[r * n + k] : 0.0;
+        for (int64_t q = 0; q < w; ++q) {
+            const int64_t r = k - 1 - q;
+            Uc[k * w + q] = r >= 0 ? A[r * n + k] : 0.0;
         }
         Ud[k] = A[k * n + k];
     }

@@ -604,18 +604,18 @@ __global__ __launch_bounds__(256) void k_copy(const T *__restrict__ a, T *__rest
 // Factors of P A = L U as the host factorisation leaves them (partial pivoting
 // interleaved with the elimination): column k of L holds kl multipliers
 // Lc[k kl + q] (row k + 1 + q); column k of U above the diagonal holds
-// Uc[k w + t] = U(k - w + t, k), w = kl + ku; Ud[k] = U(k, k); row k was
+// Uc[k w + q] = U(k - 1 - q, k), w = kl + ku; Ud[k] = U(k, k); row k was
 // swapped with row piv[k] >= k before column k was eliminated.
 //
-// A block of CI_T threads computes two columns j0, j0 + 1 of X = A^{-1} by the
+// Bands wider than CI_BAND: a block of CI_T threads computes two columns j0, j0 + 1 of X = A^{-1} by the
 // same forward and back substitution as a single solve, applied to unit
 // vectors held in LDS (Y[i 2 + r], row i of right-hand side r).  Each step is
 // one multiply-subtract of a factor column followed by a barrier; the factor
 // column, pivot and diagonal of step k + CI_D are loaded at step k into one of
 // CI_D register sets (the step loop is unrolled CI_D times so the sets stay in
 // registers) and the barrier waits for LDS only, so these loads stay in flight
-// across CI_D steps.  With LONG, columns longer than the register sets load
-// the rest directly.  Forward steps before j0 - kl only move zeros and are
+// across CI_D steps.  Columns longer than the register sets load the rest
+// directly.  Forward steps before j0 - kl only move zeros and are
 // skipped.  The back substitution finishes row k at step k and writes it to X
 // (by columns: X[j n + i] = (A^{-1})_ij).
 constexpr int CI_T = 256;
@@ -674,23 +674,23 @@ __device__ __forceinline__ void ci_load_back(int k, int w, const double *__restr
 {
     const bool live = k >= 0;
     const int rows = live ? min(w, k) : 0, cnt = rows * 2;
-    const double *col = cnt > 0 ? Uc + (int64_t)k * w + (w - rows) : Uc;
+    const double *col = cnt > 0 ? Uc + (int64_t)k * w : Uc;
     const double dl = Ud[(live ? k : 0) + ci_vzero()];
     c.d = live ? dl : 1.0;
 #pragma unroll
     for (int m = 0; m < CI_PFB; ++m) {
         const int idx = tid + CI_T * m;
-        const double t = col[idx < cnt ? idx >> 1 : 0];
+        const double t = col[idx < cnt ? rows - 1 - (idx >> 1) : 0];
         c.v[m] = idx < cnt ? t : 0.0;
     }
 }
 
-template <bool LONG>
-__global__ __launch_bounds__(CI_T) void k_coarse_inverse(int n, int kl, int w, const double *__restrict__ Lc,
-                                                         const double *__restrict__ Uc,
-                                                         const double *__restrict__ Ud,
-                                                         const int *__restrict__ piv,
-                                                         double *__restrict__ X)
+__global__ __launch_bounds__(CI_T) void k_coarse_inverse_wide(int n, int kl, int w,
+                                                              const double *__restrict__ Lc,
+                                                              const double *__restrict__ Uc,
+                                                              const double *__restrict__ Ud,
+                                                              const int *__restrict__ piv,
+                                                              double *__restrict__ X)
 {
     extern __shared__ double Y[];  // 2 n entries
     const int tid = threadIdx.x;
@@ -726,11 +726,9 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse(int n, int kl, int w, c
                     const int idx = tid + CI_T * m;
                     if (idx < cnt) yk[idx] -= F[u].v[m] * ((idx & 1) ? y1 : y0);
                 }
-                if (LONG) {
-                    const double *lk = Lc + (int64_t)k * kl;
-                    for (int idx = tid + CI_T * CI_PFF; idx < cnt; idx += CI_T)
-                        yk[idx] -= lk[idx >> 1] * ((idx & 1) ? y1 : y0);
-                }
+                const double *lk = Lc + (int64_t)k * kl;
+                for (int idx = tid + CI_T * CI_PFF; idx < cnt; idx += CI_T)
+                    yk[idx] -= lk[idx >> 1] * ((idx & 1) ? y1 : y0);
                 ci_load_fwd(k + CI_D, n, kl, Lc, piv, tid, F[u]);
                 ci_sync();
             }
@@ -754,11 +752,9 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse(int n, int kl, int w, c
                     const int idx = tid + CI_T * m;
                     if (idx < cnt) yr[idx] -= B[u].v[m] * ((idx & 1) ? x1 : x0);
                 }
-                if (LONG) {
-                    const double *uk = Uc + (int64_t)k * w + (w - rows);
-                    for (int idx = tid + CI_T * CI_PFB; idx < cnt; idx += CI_T)
-                        yr[idx] -= uk[idx >> 1] * ((idx & 1) ? x1 : x0);
-                }
+                const double *uk = Uc + (int64_t)k * w;
+                for (int idx = tid + CI_T * CI_PFB; idx < cnt; idx += CI_T)
+                    yr[idx] -= uk[rows - 1 - (idx >> 1)] * ((idx & 1) ? x1 : x0);
                 if (tid == 0) X[(int64_t)j0 * n + k] = x0;
                 if (tid == 1 && two) X[(int64_t)(j0 + 1) * n + k] = x1;
                 ci_load_back(k - CI_D, w, Uc, Ud, tid, B[u]);
@@ -766,6 +762,170 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse(int n, int kl, int w, c
             }
         }
     }
+}
+
+// The same inverse for bands up to CI_BAND, with the columns' active rows in registers.
+// The kernel above passes every step through LDS and a workgroup barrier (0.29 us a
+// step: n = 632, kl = 110: 528 us; n = 233, kl = 87: 186 us), though a column's steps
+// depend on each other only through one entry.  Here a wave has C columns: in a block of
+// 64 steps lane l holds rows 64 (m + s) + l, s < S, so a step is C readlanes of the
+// pivot row's entry and C S FMAs, with no LDS and no barrier, and its factor column is
+// loaded CI_D steps ahead.  A column's entries lie at lane + 64 s - (step + 1); the
+// buffer's range check returns zeros outside it, which are the rows not to be updated.
+// Back substitution runs the same sweep over reversed rows.  The step multiplies by the
+// diagonal's reciprocal (64 at a time); the result itself is divided.
+// What bounds it is the instructions of a step, about 16 + C (S + 4) issued one by one, and
+// from n = 700 on the factors' reads from L2, which each wave makes.  Hence C: below
+// CI_TWO one column per wave (n = 233, kl = 87: 40 us against 52 with two; n = 632,
+// kl = 110: 120 against 136), above it two (n = 700, kl = 225: 197 against 211).
+constexpr int CI_TWO = 640;
+constexpr int CI_BAND = 256;
+
+__device__ __forceinline__ double ci_lane(double v, int lane)
+{
+    union {
+        double d;
+        int i[2];
+    } a;
+    a.d = v;
+    a.i[0] = __builtin_amdgcn_readlane(a.i[0], lane);
+    a.i[1] = __builtin_amdgcn_readlane(a.i[1], lane);
+    return a.d;
+}
+
+template <int S>
+struct CiCol {
+    double v[S];
+};
+
+// The factor column at F of a step with t % 64 = k: entry o = lane + 64 s - k - 1 of ld,
+// zero outside; o0 = 8 (lane - k - 1).
+template <int S>
+__device__ __forceinline__ void ci_load(const double *F, int ld, int o0, CiCol<S> &a)
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    union {
+        u2 u;
+        double d;
+    } x;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(F), 0, 8 * ld, 0x00020000);
+    // (the second offset is hidden from the compiler: the first may be negative, and
+    // must not become the second's base)
+    int o1 = o0 + 512;
+    asm volatile("" : "+v"(o1));
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        x.u = __builtin_amdgcn_raw_buffer_load_b64(rs, s == 0 ? o0 : o1 + 512 * (s - 1), 0, 0);
+        a.v[s] = x.d;
+    }
+}
+
+// Steps m0 * 64 .. n - 1 of one triangular sweep on C columns (Y: C x n in LDS).
+// !BACK: from the unit vectors of columns j0, j0 + 1, .. with L and its row swaps, into Y.
+// BACK: from Y, its rows reversed, with U, into X.
+template <int S, int C, bool BACK>
+__device__ __forceinline__ void ci_sweep(int n, int ld, const double *__restrict__ F, int m0, int j0,
+                                         const int *__restrict__ piv, const double *__restrict__ Ud,
+                                         double *Y, double *__restrict__ X)
+{
+    const int lane = (int)threadIdx.x;
+    auto row0 = [&](int r, int c) {
+        if (!BACK) return r == j0 + c && r < n ? 1.0 : 0.0;
+        const double v = Y[c * n + (r < n ? n - 1 - r : 0)];
+        return r < n ? v : 0.0;
+    };
+    double y[S][C];
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+#pragma unroll
+        for (int c = 0; c < C; ++c) y[s][c] = row0(64 * (m0 + s) + lane, c);
+    // columns are loaded CI_D steps ahead; past the last one, the last one again (steps
+    // past n - 1 multiply it by zero)
+    CiCol<S> a[CI_D];
+    int tl = 64 * m0;
+    const double *Fl = F + (int64_t)(BACK ? n - 1 - tl : tl) * ld;
+    auto next = [&]() {
+        const double *f = Fl;
+        ++tl;
+        Fl += tl >= n ? 0 : BACK ? -(int64_t)ld : (int64_t)ld;
+        return f;
+    };
+#pragma unroll
+    for (int u = 0; u < CI_D; ++u) ci_load<S>(next(), ld, 8 * (lane - 1) - 8 * u, a[u]);
+    for (int b0 = 64 * m0; b0 < n; b0 += 64) {
+        const int mine = min(b0 + lane, n - 1);
+        const int pv = BACK ? 0 : b0 + lane < n ? piv[mine] - b0 : lane;
+        const double dg = BACK ? Ud[n - 1 - mine] : 1.0;
+        const double rd = BACK ? 1.0 / dg : 1.0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) y[S - 1][c] = row0(b0 + 64 * (S - 1) + lane, c);
+#pragma unroll 1
+        for (int k0 = 0; k0 < 64 && b0 + k0 < n; k0 += CI_D) {
+            const int on = 8 * (lane - 1 - (k0 + CI_D) % 64);
+#pragma unroll
+            for (int u = 0; u < CI_D; ++u) {
+                const int k = k0 + u;
+                if (!BACK) {
+                    const int p = __builtin_amdgcn_readlane(pv, k);
+                    if (p != k) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const double yk = ci_lane(y[0][c], k);
+                            double yp = 0.0;
+#pragma unroll
+                            for (int s = 0; s < S; ++s)
+                                if ((p >> 6) == s) {
+                                    yp = ci_lane(y[s][c], p & 63);
+                                    y[s][c] = lane == (p & 63) ? yk : y[s][c];
+                                }
+                            y[0][c] = lane == k ? yp : y[0][c];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    double x = ci_lane(y[0][c], k);
+                    if (BACK) x *= ci_lane(rd, k);
+#pragma unroll
+                    for (int s = 0; s < S; ++s) y[s][c] -= a[u].v[s] * x;
+                }
+                ci_load<S>(next(), ld, on - 8 * u, a[u]);
+            }
+        }
+        const int r = b0 + lane;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (r < n) {
+                if (!BACK)
+                    Y[c * n + r] = y[0][c];
+                else if (j0 + c < n)
+                    X[(int64_t)(j0 + c) * n + (n - 1 - r)] = y[0][c] / dg;
+            }
+#pragma unroll
+            for (int s = 0; s < S - 1; ++s) y[s][c] = y[s + 1][c];
+        }
+    }
+}
+
+// SB: 64-row slots of the back substitution, 1 + ceil((kl + ku) / 64) with kl = ku
+template <int SB, int C>
+__global__ __launch_bounds__(64) void k_coarse_inverse(int n, int kl, int w,
+                                                              const double *__restrict__ Lc,
+                                                              const double *__restrict__ Uc,
+                                                              const double *__restrict__ Ud,
+                                                              const int *__restrict__ piv,
+                                                              double *__restrict__ X)
+{
+    extern __shared__ double Y[];  // C x n
+    const int j0 = C * (int)blockIdx.x;
+    // rows before the first that the swaps can move the unit entry to stay zero
+    const int m0 = max(0, j0 - kl) >> 6;
+    for (int r = (int)threadIdx.x; r < 64 * m0; r += 64)
+#pragma unroll
+        for (int c = 0; c < C; ++c) Y[c * n + r] = 0.0;
+    ci_sweep<SB / 2 + 1, C, false>(n, kl, Lc, m0, j0, piv, Ud, Y, X);
+    ci_sweep<SB, C, true>(n, w, Uc, 0, j0, piv, Ud, Y, X);
 }
 
 // x = A^{-1} b (A^{-T} b when TR) on the coarsest level in two passes, FP64
@@ -1121,13 +1281,31 @@ hipError_t mg_stencil_diag(int64_t nn, const double *S, double *D, hipStream_t s
 hipError_t mg_coarse_inverse(int n, int kl, int ku, const double *Lc, const double *Uc,
                              const double *Ud, const int *piv, double *X, hipStream_t st)
 {
-    const unsigned lds = (unsigned)(2 * n * sizeof(double));
-    if (2 * kl <= CI_T * CI_PFF && 2 * (kl + ku) <= CI_T * CI_PFB)
-        hipLaunchKernelGGL(k_coarse_inverse<false>, dim3((unsigned)((n + 1) / 2)), dim3(CI_T), lds, st,
-                           n, kl, kl + ku, Lc, Uc, Ud, piv, X);
-    else
-        hipLaunchKernelGGL(k_coarse_inverse<true>, dim3((unsigned)((n + 1) / 2)), dim3(CI_T), lds, st,
-                           n, kl, kl + ku, Lc, Uc, Ud, piv, X);
+    const int w = kl + ku;
+    // slots that hold the back substitution's w rows and the forward one's kl
+    const int SB = std::max(1 + (w + 63) / 64, 2 * ((kl + 63) / 64));
+    if (std::max(kl, ku) > CI_BAND) {
+        hipLaunchKernelGGL(k_coarse_inverse_wide, dim3((unsigned)((n + 1) / 2)), dim3(CI_T),
+                           (unsigned)(2 * n * sizeof(double)), st, n, kl, w, Lc, Uc, Ud, piv, X);
+        return hipGetLastError();
+    }
+    const int C = n <= CI_TWO ? 1 : 2;
+    const dim3 grid((unsigned)((n + C - 1) / C)), block(64);
+    const unsigned lds = (unsigned)(C * n * sizeof(double));  // (n <= 2400)
+    switch (SB) {
+#define FE_CI(B)                                                                                   \
+    case B:                                                                                        \
+        if (C == 1)                                                                                \
+            hipLaunchKernelGGL((k_coarse_inverse<B, 1>), grid, block, lds, st, n, kl, w, Lc, Uc,   \
+                               Ud, piv, X);                                                        \
+        else                                                                                       \
+            hipLaunchKernelGGL((k_coarse_inverse<B, 2>), grid, block, lds, st, n, kl, w, Lc, Uc,   \
+                               Ud, piv, X);                                                        \
+        break;
+        FE_CI(2) FE_CI(3) FE_CI(4) FE_CI(5) FE_CI(6) FE_CI(7) FE_CI(8) FE_CI(9)
+#undef FE_CI
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@ of few nodes.  Sweeps: one and two before, none, one and two after.
 import numpy as np
 import pytest
 
+import oracle
 from paper_1508_04596_amd import inputs
 from tests.helpers import rel_norm
 
@@ -64,3 +65,29 @@ def test_fused_small_levels(fe, dims, pc, sweeps):
     assert abs(a0["lin_its_total"] - a1["lin_its_total"]) <= 1
     assert rel_norm(x1, x0) <= 1e-6
     assert rel_norm(l1, l0) <= 1e-5
+
+
+# coarsest level (half the fine counts) whose half bandwidth takes each slot count of the
+# register-resident inverse: 21, 46, 65, 101, 138, 175, 212, 249; then 671 unknowns, which
+# it takes two columns per wave for
+@pytest.mark.parametrize("dims", [(4, 4, 24), (4, 10, 8), (6, 8, 6), (6, 14, 8), (8, 14, 8), (10, 14, 8),
+                                  (12, 14, 6), (14, 14, 6), (10, 10, 14)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_coarsest_level_bands(fe, dims):
+    """An exact coarse solve on two levels: 20 Krylov steps reduce a Newton system's
+    residual enough, and the states reach the oracle's residual (the bounds of the
+    two-level slab in the solver's tests)."""
+    print(f"[coarse] {dims}", flush=True)
+    p = inputs.scaled_config(*dims, 2e3, seed=404)
+    prob = fe.Problem.from_inputs(p, mask="solve")
+    x = torch.zeros(p.n_dof, dtype=torch.float64, device="cuda")
+    rep = fe.newton_solve(prob, dev(p.gamma), dev(p.s), x,
+                          fe.solve_opts(rtol_newton=1e-8, precond="multigrid"))
+    torch.cuda.synchronize()
+    r0 = np.linalg.norm(oracle.residual(p, np.zeros(p.n_dof), mask="solve"))
+    r = np.linalg.norm(oracle.residual(p, x.cpu().numpy(), mask="solve"))
+    print(f"[coarse] newton {rep['newton_its']} lin {rep['lin_its']} rel {r / r0:.2e}")
+    assert rep["mg_levels"] == 2
+    assert r <= 1e-8 * r0 * 1.0001
+    assert max(rep["lin_its"]) <= 20
+    prob.close()
