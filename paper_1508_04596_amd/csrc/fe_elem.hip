@@ -1515,19 +1515,22 @@ __global__ __launch_bounds__(256) void kb_combine_smooth(const BElemSmooth<T> *_
 
 // Element Jacobians: thread (e, c) evaluates J_e e_c, the 40 element rows for the
 // unit direction on local DOF c = 8 f + a (corner a, field f); a prescribed DOF
-// gives a zero direction, as in fe_jvp.  Je is [element][row][column], 40 x 40.
+// gives a zero direction, as in fe_jvp.  Je is [row][column][element]: consecutive
+// elements are consecutive here and in the gathers below, which read every entry
+// once ([element][row][column] left a cache line to each lane of a wave: 114 us for the
+// stencils of a cavity's 16x16x32 and 8x8x16 levels on average, now 24).  The gathers
+// are bound by their traffic, 156 MB at 16x16x32; the Jacobians by the arithmetic of 40
+// directions an element, 54 us there.
 __global__ __launch_bounds__(64) void k_elem_jac(Geo g, const double *__restrict__ x,
                                                  const double *__restrict__ gamma,
                                                  const double *__restrict__ src,
                                                  const uint8_t *__restrict__ nmask,
                                                  double *__restrict__ Je)
 {
-    const int64_t ne = n_elem(g);
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= ne * 40) return;
-    const int64_t e = tid / 40;
-    const int col = (int)(tid - e * 40);
-    const int i = (int)(e % g.nx), j = (int)((e / g.nx) % g.ny), k = (int)(e / ((int64_t)g.nx * g.ny));
+    const int ne = (int)n_elem(g);  // (1600 ne entries fit the device)
+    const int e = (int)(blockIdx.x * blockDim.x + threadIdx.x), col = (int)blockIdx.y;
+    if (e >= ne) return;
+    const int i = e % g.nx, r = e / g.nx, j = r % g.ny, k = r / g.ny;
     int64_t nd[8];
 #pragma unroll
     for (int a = 0; a < 8; ++a) nd[a] = gnode(g, i + (a & 1), j + ((a >> 1) & 1), k + (a >> 2));
@@ -1543,7 +1546,7 @@ __global__ __launch_bounds__(64) void k_elem_jac(Geo g, const double *__restrict
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) Je[(e * 40 + 8 * f + a) * 40 + col] = R[f][a];
+        for (int a = 0; a < 8; ++a) Je[((8 * f + a) * 40 + col) * (int64_t)ne + e] = R[f][a];
 }
 
 // The 135 probing products J p_q of a small grid from its element Jacobians:
@@ -1581,7 +1584,7 @@ __global__ __launch_bounds__(256) void k_probe_from_jac(Geo g, const double *__r
                 for (int b = 0; b < 8; ++b) {
                     const int mi = ei + (b & 1), mj = ej + ((b >> 1) & 1), mk = ek + (b >> 2);
                     if ((mi % 3) + 3 * (mj % 3) + 9 * (mk % 3) != colr) continue;
-                    acc += Je[(e * 40 + 8 * gr + aN) * 40 + 8 * f + b];
+                    acc += Je[((8 * gr + aN) * 40 + 8 * f + b) * n_elem(g) + e];
                     break;
                 }
             }
@@ -1599,15 +1602,13 @@ __global__ __launch_bounds__(256) void k_stencil_from_jac(Geo g, const double *_
                                                           const uint8_t *__restrict__ nmask,
                                                           double *__restrict__ S)
 {
-    const int64_t nn = n_nodes(g);
-    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= 675 * nn) return;
-    const int q = (int)(tid / nn);
-    const int64_t N = tid - (int64_t)q * nn;
+    const int nn = (int)n_nodes(g), ne = (int)n_elem(g);  // (675 nn entries fit the device)
+    const int N = (int)(blockIdx.x * blockDim.x + threadIdx.x), q = (int)blockIdx.y;
+    if (N >= nn) return;
+    const int64_t tid = (int64_t)q * nn + N;
     const int d = q / 25, gr = (q / NF) % NF, f = q % NF;
     const int ddx = d % 3 - 1, ddy = (d / 3) % 3 - 1, ddz = d / 9 - 1;
-    const int I = (int)(N % (g.nx + 1)), J = (int)((N / (g.nx + 1)) % (g.ny + 1)),
-              K = (int)(N / ((int64_t)(g.nx + 1) * (g.ny + 1)));
+    const int I = N % (g.nx + 1), r = N / (g.nx + 1), J = r % (g.ny + 1), K = r / (g.ny + 1);
     if ((nmask[N] >> gr) & 1) {
         S[tid] = (d == 13 && f == gr) ? 1.0 : 0.0;
         return;
@@ -1621,10 +1622,10 @@ __global__ __launch_bounds__(256) void k_stencil_from_jac(Geo g, const double *_
                 // corners of N and of M in this element
                 const int bx = -dx + ddx, by = -dy + ddy, bz = -dz + ddz;
                 if (bx < 0 || bx > 1 || by < 0 || by > 1 || bz < 0 || bz > 1) continue;
-                const int64_t e = ei + (int64_t)g.nx * (ej + (int64_t)g.ny * ek);
+                const int e = ei + g.nx * (ej + g.ny * ek);
                 const int aN = (-dx) | ((-dy) << 1) | ((-dz) << 2);
                 const int b = bx | (by << 1) | (bz << 2);
-                acc += Je[(e * 40 + 8 * gr + aN) * 40 + 8 * f + b];
+                acc += Je[((8 * gr + aN) * 40 + 8 * f + b) * (int64_t)ne + e];
             }
     S[tid] = acc;
 }
@@ -1769,9 +1770,9 @@ hipError_t launch_stencil_assemble(const Geo &g, const double *x, const double *
                                    hipStream_t st)
 {
     const int64_t ne = n_elem(g), nn = n_nodes(g);
-    hipLaunchKernelGGL(k_elem_jac, dim3((unsigned)((ne * 40 + 63) / 64)), dim3(64), 0, st, g, x,
+    hipLaunchKernelGGL(k_elem_jac, dim3((unsigned)((ne + 63) / 64), 40), dim3(64), 0, st, g, x,
                        gamma, s, nmask, Je);
-    hipLaunchKernelGGL(k_stencil_from_jac, dim3((unsigned)((675 * nn + 255) / 256)), dim3(256), 0,
+    hipLaunchKernelGGL(k_stencil_from_jac, dim3((unsigned)((nn + 255) / 256), 675), dim3(256), 0,
                        st, g, (const double *)Je, nmask, S);
     return hipGetLastError();
 }
@@ -1781,7 +1782,7 @@ hipError_t launch_probe_products(const Geo &g, const double *x, const double *ga
                                  double *probe_out, hipStream_t st)
 {
     const int64_t ne = n_elem(g), ndof = NF * n_nodes(g);
-    hipLaunchKernelGGL(k_elem_jac, dim3((unsigned)((ne * 40 + 63) / 64)), dim3(64), 0, st, g, x,
+    hipLaunchKernelGGL(k_elem_jac, dim3((unsigned)((ne + 63) / 64), 40), dim3(64), 0, st, g, x,
                        gamma, s, nmask, Je);
     hipLaunchKernelGGL(k_probe_from_jac, dim3((unsigned)((135 * ndof + 255) / 256)), dim3(256), 0,
                        st, g, (const double *)Je, nmask, probe_out);

@@ -766,7 +766,7 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse_wide(int n, int kl, int
 
 // The same inverse for bands up to CI_BAND, with the columns' active rows in registers.
 // The kernel above passes every step through LDS and a workgroup barrier (0.29 us a
-// step: n = 632, kl = 110: 528 us; n = 233, kl = 87: 186 us), though a column's steps
+// step: n = 632, kl = 110: 528 us, here 147; n = 233, kl = 87: 186 us, here 54), though a column's steps
 // depend on each other only through one entry.  Here a wave has C columns: in a block of
 // 64 steps lane l holds rows 64 (m + s) + l, s < S, so a step is C readlanes of the
 // pivot row's entry and C S FMAs, with no LDS and no barrier, and its factor column is
@@ -776,8 +776,9 @@ __global__ __launch_bounds__(CI_T) void k_coarse_inverse_wide(int n, int kl, int
 // diagonal's reciprocal (64 at a time); the result itself is divided.
 // What bounds it is the instructions of a step, about 16 + C (S + 4) issued one by one, and
 // from n = 700 on the factors' reads from L2, which each wave makes.  Hence C: below
-// CI_TWO one column per wave (n = 233, kl = 87: 40 us against 52 with two; n = 632,
-// kl = 110: 120 against 136), above it two (n = 700, kl = 225: 197 against 211).
+// CI_TWO one column per wave (without row swaps, n = 233, kl = 87: 40 us against 52 with
+// two; n = 632, kl = 110: 120 against 136), above it two (n = 700, kl = 225: 197 against
+// 211).
 constexpr int CI_TWO = 640;
 constexpr int CI_BAND = 256;
 
