@@ -164,6 +164,151 @@ int mg_num_levels(const fe_grid &g)
     return n ? n : count_levels(g, true);
 }
 
+// ---- band LU of the coarsest matrix (host) ------------------------------------
+
+// Row i of the band matrix holds columns i - kl - LU_NB .. i + kl + ku + LU_NB (the
+// fill of row swaps, and a panel's width on both sides), row after row.
+constexpr int LU_NB = 8;
+static int64_t lu_row(int64_t kl, int64_t ku) { return 2 * kl + ku + 2 * LU_NB + 1; }
+
+struct BandMatrix {
+    double *a;
+    int64_t step, off;
+    BandMatrix(double *w, int64_t kl, int64_t ku) : a(w), step(lu_row(kl, ku) - 1), off(kl + LU_NB) {}
+    double *row(int64_t i) const { return a + i * step + off; }  // indexed by column
+};
+
+// r[0 .. n) -= sum_c l[c] u[c ustep + 0 .. n), c < LU_NB: V doubles at a time.
+template <typename V>
+__attribute__((always_inline)) static inline void lu_update(double *r, const double *l,
+                                                            const double *u, int64_t ustep,
+                                                            int64_t n)
+{
+    constexpr int W = sizeof(V) / sizeof(double);
+    typedef V U __attribute__((aligned(8)));
+    V lv[LU_NB];
+    for (int c = 0; c < LU_NB; ++c) lv[c] = l[c] - V{};
+    int64_t j = 0;
+    for (; j + 2 * W <= n; j += 2 * W) {
+        V s0{}, s1{}, t0{}, t1{};
+#pragma unroll
+        for (int c = 0; c < LU_NB; c += 2) {
+            s0 += lv[c] * *(const U *)(u + c * ustep + j);
+            s1 += lv[c] * *(const U *)(u + c * ustep + j + W);
+            t0 += lv[c + 1] * *(const U *)(u + (c + 1) * ustep + j);
+            t1 += lv[c + 1] * *(const U *)(u + (c + 1) * ustep + j + W);
+        }
+        *(U *)(r + j) = *(const U *)(r + j) - (s0 + t0);
+        *(U *)(r + j + W) = *(const U *)(r + j + W) - (s1 + t1);
+    }
+    for (; j < n; ++j) {
+        double s = 0.0;
+        for (int c = 0; c < LU_NB; ++c) s += l[c] * u[c * ustep + j];
+        r[j] -= s;
+    }
+}
+typedef double lu_v4 __attribute__((vector_size(32)));
+typedef double lu_v8 __attribute__((vector_size(64)));
+
+// Rows i0 .. i1 of the trailing matrix, columns j0 .. j0 + n - 1, less the panel's
+// product: P holds the panel by columns (pr rows each), its first row is row k0.
+#define FE_LU_TRAILING                                                                            \
+    for (int64_t i = i0; i < i1; ++i) {                                                            \
+        double l[LU_NB];                                                                           \
+        bool any = false;                                                                          \
+        for (int c = 0; c < LU_NB; ++c) {                                                          \
+            l[c] = P[c * pr + (i - k0)];                                                           \
+            any |= l[c] != 0.0;                                                                    \
+        }                                                                                          \
+        if (any) lu_update<V>(A.row(i) + j0, l, A.row(k0) + j0, A.step, n);                        \
+    }
+static void lu_trailing(const BandMatrix &A, const double *P, int64_t pr, int64_t k0, int64_t i0,
+                        int64_t i1, int64_t j0, int64_t n)
+{
+    typedef lu_v4 V;
+    FE_LU_TRAILING
+}
+__attribute__((target("avx512f"))) static void lu_trailing512(const BandMatrix &A, const double *P,
+                                                              int64_t pr, int64_t k0, int64_t i0,
+                                                              int64_t i1, int64_t j0, int64_t n)
+{
+    typedef lu_v8 V;
+    FE_LU_TRAILING
+}
+#undef FE_LU_TRAILING
+
+// Band LU with partial pivoting of the n x n matrix A, LU_NB columns at a time: the
+// panel is factored in a buffer by columns, and its row operations are applied to the
+// rest of the band together.  The GPU waits for this; one column at a time read and
+// wrote the whole window, 200 KB, for every column: n = 632, kl = 110: 1.24 ms, here
+// 0.60; n = 233, kl = 87: 0.24, here 0.13.  (One workgroup on the device, its window in
+// registers, took 1.1 and 0.36 ms: a step's pivot search is a chain of instructions that
+// nothing else on the CU fills.)  Lc, Uc, Ud, piv: the layout the device inverse reads
+// (multipliers as they were in step k, before later swaps).  False: zero or non-finite
+// pivot.
+static bool band_lu_factor(int64_t n, int kl, int ku, double *Aw, double *Lc, double *Uc, double *Ud,
+                           int *piv, double *panel)
+{
+    const BandMatrix A(Aw, kl, ku);
+    const int64_t w = kl + ku, pr = LU_NB + kl;
+    static const bool wide = __builtin_cpu_supports("avx512f");
+    double *P = panel;
+    for (int64_t k0 = 0; k0 < n; k0 += LU_NB) {
+        const int64_t nb = std::min<int64_t>(LU_NB, n - k0), j0 = k0 + nb;
+        const int64_t m = std::min<int64_t>(n, j0 + kl) - k0;        // panel rows
+        const int64_t nt = std::min<int64_t>(n, j0 + w) - j0;        // columns right of the panel
+        for (int64_t i = 0; i < m; ++i)
+            for (int64_t c = 0; c < nb; ++c) P[c * pr + i] = A.row(k0 + i)[k0 + c];
+        for (int64_t c = 0; c < nb; ++c) {
+            const int64_t k = k0 + c, ie = std::min<int64_t>(m, c + 1 + kl);
+            double *pc = P + c * pr;
+            int64_t p = c;
+            double best = std::fabs(pc[c]);
+            for (int64_t i = c + 1; i < ie; ++i)
+                if (std::fabs(pc[i]) > best) {
+                    best = std::fabs(pc[i]);
+                    p = i;
+                }
+            piv[k] = (int)(k0 + p);
+            if (best == 0.0 || !std::isfinite(best)) return false;
+            if (p != c) {
+                for (int64_t q = 0; q < nb; ++q) std::swap(P[q * pr + c], P[q * pr + p]);
+                std::swap_ranges(A.row(k) + j0, A.row(k) + j0 + nt, A.row(k0 + p) + j0);
+            }
+            const double inv = 1.0 / pc[c];
+            double *lc = Lc + k * kl;
+            for (int64_t i = c + 1; i < ie; ++i) lc[i - c - 1] = pc[i] *= inv;
+            for (int64_t i = ie - c - 1; i < kl; ++i) lc[i] = 0.0;
+            for (int64_t q = c + 1; q < nb; ++q) {
+                double *pq = P + q * pr;
+                const double u = pq[c];
+                if (u != 0.0)
+                    for (int64_t i = c + 1; i < ie; ++i) pq[i] -= pc[i] * u;
+            }
+        }
+        // the panel's rows of U right of it, and U by columns: Uc[k w + q] = U(k - 1 - q, k)
+        for (int64_t c = 1; c < nb; ++c)
+            for (int64_t q = 0; q < c; ++q) {
+                const double l = P[q * pr + c], *rq = A.row(k0 + q) + j0;
+                double *rc = A.row(k0 + c) + j0;
+                if (l != 0.0)
+                    for (int64_t j = 0; j < nt; ++j) rc[j] -= l * rq[j];
+            }
+        for (int64_t c = 0; c < nb; ++c) {
+            Ud[k0 + c] = P[c * pr + c];
+            for (int64_t q = 0; q < std::min(c, w); ++q) Uc[(k0 + c) * w + q] = P[c * pr + c - 1 - q];
+            const double *rc = A.row(k0 + c) + j0;
+            double *u = Uc + j0 * w + (nb - 1 - c);
+            for (int64_t j = 0; j < std::min(nt, w - (nb - 1 - c)); ++j) u[j * (w + 1)] = rc[j];
+        }
+        if (nb < LU_NB) break;  // (the last panel: nothing below it)
+        (wide ? lu_trailing512 : lu_trailing)(A, P, pr, k0, j0, k0 + m, j0, nt);
+    }
+    for (int64_t k = 0; k < std::min(n, w); ++k)
+        std::fill(Uc + k * w + k, Uc + (k + 1) * w, 0.0);
+    return true;
+}
+
 static int64_t r256(int64_t b) { return (b + 255) / 256 * 256; }
 
 // Half bandwidth of the coarsest matrix in lexicographic node order, NF DOF per node.
@@ -288,7 +433,8 @@ int mg_create(fe_problem *p, bool mixed, int64_t asm_nodes, Mg **out)
         mg_free(mg);
         return hip_fail(e, "hipMalloc (multigrid)");
     }
-    mg->A.assign((size_t)C.ndof * C.ndof, 0.0);
+    mg->A.assign((size_t)C.ndof * lu_row(bw, bw), 0.0);
+    mg->panel.assign((size_t)LU_NB * (LU_NB + bw), 0.0);
     *out = mg;
     return FE_OK;
 }
@@ -330,113 +476,84 @@ static void condense_coarse(Mg *mg, const fe_grid &grid)
     }
     mg->nf = m;
     const int nx = grid.nx, ny = grid.ny, nz = grid.nz;
-    int64_t lo = 0, hi = 0;
+    // first and last free DOF of a node (first > last: none)
+    auto first = [&](int64_t N) {
+        int64_t r = n;
+        for (int g = 0; g < NF; ++g)
+            if (pos[NF * N + g] >= 0) r = std::min<int64_t>(r, pos[NF * N + g]);
+        return r;
+    };
+    auto last = [&](int64_t N) {
+        int64_t r = -1;
+        for (int g = 0; g < NF; ++g) r = std::max<int64_t>(r, pos[NF * N + g]);
+        return r;
+    };
+    int64_t half = 0;  // (nodes are neighbours both ways: kl = ku)
     for (int K = 0; K <= nz; ++K)
         for (int J = 0; J <= ny; ++J)
             for (int I = 0; I <= nx; ++I) {
                 const int64_t N = I + (int64_t)(nx + 1) * (J + (int64_t)(ny + 1) * K);
-                for (int dz = -1; dz <= 1; ++dz)
+                const int64_t r = last(N);
+                if (r < 0) continue;
+                for (int dz = -1; dz <= 0; ++dz)  // (later nodes have later DOFs)
                     for (int dy = -1; dy <= 1; ++dy)
                         for (int dx = -1; dx <= 1; ++dx) {
                             const int i = I + dx, j = J + dy, k = K + dz;
-                            if (i < 0 || j < 0 || k < 0 || i > nx || j > ny || k > nz) continue;
+                            if (i < 0 || j < 0 || k < 0 || i > nx || j > ny) continue;
                             const int64_t M = i + (int64_t)(nx + 1) * (j + (int64_t)(ny + 1) * k);
-                            for (int g = 0; g < NF; ++g) {
-                                const int r = pos[NF * N + g];
-                                if (r < 0) continue;
-                                for (int f = 0; f < NF; ++f) {
-                                    const int c = pos[NF * M + f];
-                                    if (c < 0) continue;
-                                    lo = std::max<int64_t>(lo, r - c);
-                                    hi = std::max<int64_t>(hi, c - r);
-                                }
-                            }
+                            half = std::max(half, r - first(M));
                         }
             }
     // at least one sub- and super-diagonal (zero ones where the matrix has none)
-    mg->kl = (int)std::min<int64_t>(std::max<int64_t>(lo, 1), mg->bw);
-    mg->ku = (int)std::min<int64_t>(std::max<int64_t>(hi, 1), mg->bw);
+    mg->kl = mg->ku = (int)std::min<int64_t>(std::max<int64_t>(half, 1), mg->bw);
 }
 
-// The coarsest matrix restricted to its free DOFs, dense row-major nf x nf, from
+// The coarsest matrix restricted to its free DOFs (m of them), as a band matrix, from
 // the 135 colour-by-field probing products: entry (pos[N g], pos[M f]) is row
-// N g of product (colour(M), f), M within one node of N, both DOFs free.
+// N g of product (colour(M), f), M within one node of N, both DOFs free.  The products
+// have just come from the device: they are read front to back (240 us at 1125 DOFs entry
+// by entry, 130 this way).
 static void assemble_free_from_probes(const fe_grid &grid, const double *probe, const int *pos,
-                                      int64_t m, double *A)
+                                      int64_t m, int kl, int ku, double *Aw)
 {
     const int nx = grid.nx, ny = grid.ny, nz = grid.nz;
-    const int64_t n = NF * (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
-    std::fill(A, A + m * m, 0.0);
-    for (int K = 0; K <= nz; ++K)
-        for (int J = 0; J <= ny; ++J)
-            for (int I = 0; I <= nx; ++I) {
-                const int64_t N = I + (int64_t)(nx + 1) * (J + (int64_t)(ny + 1) * K);
-                for (int dz = -1; dz <= 1; ++dz)
-                    for (int dy = -1; dy <= 1; ++dy)
-                        for (int dx = -1; dx <= 1; ++dx) {
-                            const int i = I + dx, j = J + dy, k = K + dz;
-                            if (i < 0 || j < 0 || k < 0 || i > nx || j > ny || k > nz) continue;
-                            const int64_t M = i + (int64_t)(nx + 1) * (j + (int64_t)(ny + 1) * k);
-                            const int col = (i % 3) + 3 * (j % 3) + 9 * (k % 3);
-                            for (int g = 0; g < NF; ++g) {
-                                const int r = pos[NF * N + g];
-                                if (r < 0) continue;
-                                for (int f = 0; f < NF; ++f) {
-                                    const int c = pos[NF * M + f];
-                                    if (c >= 0) A[r * m + c] = probe[(int64_t)(NF * col + f) * n + NF * N + g];
-                                }
-                            }
-                        }
+    std::fill(Aw, Aw + m * lu_row(kl, ku), 0.0);
+    const BandMatrix A(Aw, kl, ku);
+    // the neighbour (or itself) of index i whose index mod 3 is c, or -1
+    auto near = [](int i, int c, int n) {
+        const int j = i + (c - i % 3 + 4) % 3 - 1;
+        return j <= n ? j : -1;
+    };
+    for (int q = 0; q < 135; ++q) {
+        const int col = q / NF, f = q % NF, ci = col % 3, cj = col / 3 % 3, ck = col / 9;
+        for (int K = 0; K <= nz; ++K)
+            for (int J = 0; J <= ny; ++J) {
+                const int k = near(K, ck, nz), j = near(J, cj, ny);
+                const int64_t N0 = (int64_t)(nx + 1) * (J + (int64_t)(ny + 1) * K);
+                const int64_t M0 = (int64_t)(nx + 1) * (j + (int64_t)(ny + 1) * k);
+                if (k >= 0 && j >= 0)
+                    for (int I = 0; I <= nx; ++I) {
+                        const int i = near(I, ci, nx);
+                        const int c = i < 0 ? -1 : pos[NF * (M0 + i) + f];
+                        if (c < 0) continue;
+                        const int *r = pos + NF * (N0 + I);
+                        for (int g = 0; g < NF; ++g)
+                            if (r[g] >= 0) A.row(r[g])[c] = probe[NF * (N0 + I) + g];
+                    }
             }
+        probe += NF * (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
+    }
 }
 
-// Band LU with partial pivoting of the dense-stored condensed coarsest matrix
-// (nf x nf); the factors go to the pinned buffers in the layout the device
-// inverse reads.
+// Band LU of the condensed coarsest matrix in mg->A; the factors go to the pinned
+// buffers in the layout the device inverse reads.
 static int band_lu(Mg *mg)
 {
-    const int64_t n = mg->nf;
-    const int kl = mg->kl, ku = mg->ku;
-    const int64_t w = kl + ku;
-    double *A = mg->A.data();
-    double *Lc = mg->hfac, *Uc = Lc + n * kl, *Ud = Uc + n * w;
-    int *piv = mg->hpiv;
-    for (int64_t k = 0; k < n; ++k) {
-        const int64_t iend = std::min<int64_t>(n - 1, k + kl);
-        int64_t p = k;
-        double best = std::fabs(A[k * n + k]);
-        for (int64_t i = k + 1; i <= iend; ++i)
-            if (std::fabs(A[i * n + k]) > best) {
-                best = std::fabs(A[i * n + k]);
-                p = i;
-            }
-        piv[k] = (int)p;
-        if (best == 0.0 || !std::isfinite(best)) {
-            set_error("multigrid: singular or non-finite coarsest-level matrix");
-            return FE_ENAN;
-        }
-        const int64_t jend = std::min<int64_t>(n - 1, k + kl + ku);
-        if (p != k)
-            for (int64_t j = k; j <= jend; ++j) std::swap(A[k * n + j], A[p * n + j]);
-        const double inv = 1.0 / A[k * n + k];
-        for (int64_t i = k + 1; i <= iend; ++i) {
-            const double l = A[i * n + k] * inv;
-            A[i * n + k] = l;
-            Lc[k * kl + (i - k - 1)] = l;
-            if (l != 0.0)
-                for (int64_t j = k + 1; j <= jend; ++j) A[i * n + j] -= l * A[k * n + j];
-        }
-        for (int64_t i = iend + 1; i <= k + kl; ++i) Lc[k * kl + (i - k - 1)] = 0.0;
-    }
-    // U by columns: Uc[k w + q] = U(k - 1 - q, k), and its diagonal
-    for (int64_t k = 0; k < n; ++k) {
-        for (int64_t q = 0; q < w; ++q) {
-            const int64_t r = k - 1 - q;
-            Uc[k * w + q] = r >= 0 ? A[r * n + k] : 0.0;
-        }
-        Ud[k] = A[k * n + k];
-    }
-    return FE_OK;
+    const int64_t n = mg->nf, w = mg->kl + mg->ku;
+    double *Lc = mg->hfac, *Uc = Lc + n * mg->kl, *Ud = Uc + n * w;
+    if (band_lu_factor(n, mg->kl, mg->ku, mg->A.data(), Lc, Uc, Ud, mg->hpiv, mg->panel.data())) return FE_OK;
+    set_error("multigrid: singular or non-finite coarsest-level matrix");
+    return FE_ENAN;
 }
 
 // Per Newton step, in two calls around the caller's own fine-level set-up:
@@ -515,7 +632,8 @@ int mg_setup_finish(Mg *mg, fe_problem *p, const double *D0, const float *D032, 
     // factorisation below rewrites it)
     FE_CHECK_HIP(hipEventSynchronize(mg->probe_ready));
     condense_coarse(mg, C.grid);
-    assemble_free_from_probes(C.grid, mg->hbuf, mg->hmap + mg->nc, mg->nf, mg->A.data());
+    assemble_free_from_probes(C.grid, mg->hbuf, mg->hmap + mg->nc, mg->nf, mg->kl, mg->ku,
+                              mg->A.data());
     int rc = band_lu(mg);
     if (rc) return rc;
     // the factors and index maps to the device, then the inverse column by column

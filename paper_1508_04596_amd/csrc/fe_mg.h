@@ -34,13 +34,13 @@ struct Mg {
     bool mixed = false;
     int nu1 = 2, nu2 = 1;  // smoothing sweeps before and after the coarse-grid correction
     double omega = 0.6;
-    // coarsest level: band LU on the host of the dense-stored matrix restricted
-    // to its nf free DOFs, explicit inverse from its factors on the device
+    // coarsest level: band LU on the host of the matrix restricted to its nf
+    // free DOFs, explicit inverse from its factors on the device
     int64_t nc = 0;          // DOFs of the coarsest level
     int64_t nf = 0;          // of which not prescribed (set per Newton step from the mask)
     int bw = 0;              // half bandwidth of the full coarsest matrix (buffer sizing)
     int kl = 0, ku = 0;      // half bandwidths of the condensed matrix (<= bw)
-    std::vector<double> A;   // dense work matrix of the factorisation, nf x nf
+    std::vector<double> A, panel;  // the factorisation's band matrix and panel
     double *hfac = nullptr;  // pinned: L by columns [nf kl], U above the diagonal by columns
                              // [nf (kl + ku)], diagonal of U [nf]
     int *hpiv = nullptr;     // pinned: pivot rows [nf]
