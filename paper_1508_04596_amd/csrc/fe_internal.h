@@ -170,9 +170,11 @@ template <typename Tm, typename Tin, typename Tout>
 hipError_t launch_block_apply(const Tm *D, const Tin *v, Tout *z, int64_t nn, bool transpose,
                               const double *scale_dev, hipStream_t st);
 // out[j] = sum_{b < nparts} partial[j*RED_BLOCKS + b] (+ add[j] if add != NULL),
-// j < k, summed in a fixed order; if sqrt_last, out[k-1] = sqrt(out[k-1]).
+// j < k, summed in a fixed order; if sqrt_last, out[k-1] = sqrt(out[k-1]).  host: if not
+// NULL, device-visible pinned memory that receives them too.
 hipError_t launch_reduce(const double *partial, int k, double *out, const double *add,
-                         bool sqrt_last, hipStream_t st, int nparts = RED_BLOCKS);
+                         bool sqrt_last, hipStream_t st, int nparts = RED_BLOCKS,
+                         double *host = nullptr);
 // Workgroups (and partials per sum) of the Krylov vectors' reductions over n
 // entries: at least two entries per thread, at most RED_BLOCKS (reached from
 // n = 512 RED_BLOCKS on); short vectors thus avoid a grid of mostly idle
@@ -196,14 +198,16 @@ constexpr int PARTIAL_COLS = 130;
 // t = <c, w> at 2J + 1, e = <w, w> at 2J + 2, sigma = |c - sum s_i q_i|, the
 // coefficient h = <q_J, w> and omega = |w| at 2J + 3 .. 2J + 5 and the squared
 // norm of the next candidate at 2J + 8 (sigma = 0: nothing left of the
-// candidate, q_J = 0).  0 <= J <= 63.
+// candidate, q_J = 0); so does host, if not NULL (device-visible pinned memory).
+// 0 <= J <= 63.
 hipError_t launch_dgs_step(double *V, int64_t ld, int J, int64_t n, double *hb, double *partial,
-                           hipStream_t st);
+                           double *host, hipStream_t st);
 // The candidate's dot products alone (no new Krylov vector; it finishes the
-// last Hessenberg column of a cycle): hb[i] = <q_i, c> for i < J, hb[J] = <c, c>.
+// last Hessenberg column of a cycle): hb[i] = <q_i, c> for i < J, hb[J] = <c, c>, and
+// host as above.
 // 1 <= J <= 64.
 hipError_t launch_dgs_final(const double *V, int64_t ld, int J, int64_t n, double *hb,
-                            double *partial, hipStream_t st);
+                            double *partial, double *host, hipStream_t st);
 // Givens rotations of the FGMRES least-squares problem (host): column c of H
 // (m columns, row-major (m + 1) x m, entries 0 .. c+1 set) gets the rotations
 // 0 .. c-1, defines rotation c and advances g; returns the residual estimate
@@ -218,9 +222,8 @@ hipError_t launch_axpby(int64_t n, double a, const double *x, double b, double *
 // y = x + lam*d
 hipError_t launch_xpld(int64_t n, const double *x, double lam, const double *d, double *y,
                        hipStream_t st);
-// y = x / s[0] (s on device)
-hipError_t launch_scale_div(int64_t n, const double *x, const double *s, double *y,
-                            hipStream_t st);
+// y = x / s
+hipError_t launch_scale_div(int64_t n, const double *x, double s, double *y, hipStream_t st);
 // y += sum_j c[j] Z_j with Z of type Tz (c on device)
 template <typename Tz>
 hipError_t launch_combine(const Tz *Z, int64_t ld, int k, const double *c, double *y, int64_t n,

@@ -31,9 +31,10 @@ struct SolverWs {
     double *R = nullptr, *Rh = nullptr, *R1 = nullptr, *xt = nullptr, *delta = nullptr;
     double *rhs = nullptr, *V = nullptr, *Z = nullptr, *D = nullptr, *tmp = nullptr;
     float *Z32 = nullptr, *D32 = nullptr, *x32 = nullptr;
-    double *hbuf = nullptr;  // device: Gram-Schmidt products of a step | [255] cycle scale
+    double *hbuf = nullptr;  // device: Gram-Schmidt products of a step
     double *ydev = nullptr;  // device: combination coefficients
-    double *hhost = nullptr; // pinned host copy of hbuf / y
+    double *hhost = nullptr; // host copy of hbuf / y, pinned unless a server's pool is full
+    double *hmap = nullptr;  // hhost if kernels can write it (pinned), or null: copy hbuf
     // 0-2 / 8-10: preconditioner start, operator start, operator end of even /
     // odd Arnoldi steps; 3: Gram-Schmidt end; 4-5: set-up; 6: batched job;
     // 11: a step's results copied; 12-13: the candidate-only dot pass
@@ -98,6 +99,12 @@ static int ensure_ws(fe_problem *p, int m, bool mixed)
     if (e == hipSuccess) e = dalloc(p, &w->hbuf, sizeof(double) * 256);
     if (e == hipSuccess) e = dalloc(p, &w->ydev, sizeof(double) * 256);
     if (e == hipSuccess) e = halloc(p, &w->hhost, sizeof(double) * 256);
+    if (e == hipSuccess) {
+        // (pinned memory has one address; anything else is copied)
+        void *dev = nullptr;
+        if (hipHostGetDevicePointer(&dev, w->hhost, 0) != hipSuccess) (void)hipGetLastError();
+        w->hmap = dev == w->hhost ? w->hhost : nullptr;
+    }
     for (auto &ev : w->ev)
         if (e == hipSuccess) e = hipEventCreate(&ev);
     if (e == hipSuccess && !p->slots25)
@@ -114,10 +121,13 @@ static int ensure_ws(fe_problem *p, int m, bool mixed)
 static int norm2(fe_problem *p, const double *a, hipStream_t st, double *out)
 {
     FE_CHECK_HIP(launch_norm2_partial(a, p->ndof, p->partial, st));
-    FE_CHECK_HIP(launch_reduce(p->partial, 1, p->scal, nullptr, true, st, red_blocks(p->ndof)));
-    FE_CHECK_HIP(hipMemcpyAsync(p->ws->hhost, p->scal, sizeof(double), hipMemcpyDeviceToHost, st));
+    SolverWs *w = p->ws;
+    FE_CHECK_HIP(launch_reduce(p->partial, 1, p->scal, nullptr, true, st, red_blocks(p->ndof),
+                               w->hmap));
+    if (!w->hmap)
+        FE_CHECK_HIP(hipMemcpyAsync(w->hhost, p->scal, sizeof(double), hipMemcpyDeviceToHost, st));
     FE_CHECK_HIP(hipStreamSynchronize(st));
-    *out = p->ws->hhost[0];
+    *out = w->hhost[0];
     return FE_OK;
 }
 
@@ -233,10 +243,7 @@ static int fgmres(fe_problem *p, const LinSys &L, const double *b, double *x, do
     constexpr double SPEC_MARGIN = 100.0;
     while (true) {
         // candidate c_0 = r / beta (r = beta c_0)
-        w->hhost[200] = beta;
-        FE_CHECK_HIP(hipMemcpyAsync(w->hbuf + 255, w->hhost + 200, sizeof(double),
-                                    hipMemcpyHostToDevice, st));
-        FE_CHECK_HIP(launch_scale_div(n, r, w->hbuf + 255, w->V, st));
+        FE_CHECK_HIP(launch_scale_div(n, r, beta, w->V, st));
         std::fill(g.begin(), g.end(), 0.0);
         double om = beta, c2 = 1.0;  // scale and squared norm of the candidate
         double res = beta;
@@ -274,10 +281,11 @@ static int fgmres(fe_problem *p, const LinSys &L, const double *b, double *x, do
                 }
                 if (fin) {
                     FE_CHECK_HIP(hipEventRecord(w->ev[12], st));
-                    FE_CHECK_HIP(launch_dgs_final(w->V, ld, j, n, w->hbuf, p->partial, st));
+                    FE_CHECK_HIP(launch_dgs_final(w->V, ld, j, n, w->hbuf, p->partial, w->hmap, st));
                     FE_CHECK_HIP(hipEventRecord(w->ev[13], st));
-                    FE_CHECK_HIP(hipMemcpyAsync(w->hhost, w->hbuf, sizeof(double) * (j + 1),
-                                                hipMemcpyDeviceToHost, st));
+                    if (!w->hmap)
+                        FE_CHECK_HIP(hipMemcpyAsync(w->hhost, w->hbuf, sizeof(double) * (j + 1),
+                                                    hipMemcpyDeviceToHost, st));
                     FE_CHECK_HIP(hipStreamSynchronize(st));
                     float ms;
                     if (hipEventElapsedTime(&ms, w->ev[12], w->ev[13]) == hipSuccess) stats->t_orth += ms * 1e-3;
@@ -303,10 +311,11 @@ static int fgmres(fe_problem *p, const LinSys &L, const double *b, double *x, do
             hipEvent_t *E = step_events(j);
             if (!spec) FE_CHECK_HIP(enqueue_step(j));
             spec = false;
-            FE_CHECK_HIP(launch_dgs_step(w->V, ld, j, n, w->hbuf, p->partial, st));
+            FE_CHECK_HIP(launch_dgs_step(w->V, ld, j, n, w->hbuf, p->partial, w->hmap, st));
             FE_CHECK_HIP(hipEventRecord(w->ev[3], st));
-            FE_CHECK_HIP(hipMemcpyAsync(w->hhost, w->hbuf, sizeof(double) * (2 * j + 9),
-                                        hipMemcpyDeviceToHost, st));
+            if (!w->hmap)
+                FE_CHECK_HIP(hipMemcpyAsync(w->hhost, w->hbuf, sizeof(double) * (2 * j + 9),
+                                            hipMemcpyDeviceToHost, st));
             FE_CHECK_HIP(hipEventRecord(w->ev[11], st));
             if (res > SPEC_MARGIN * target && j + 1 < m && stats->its + 1 < max_its) {
                 FE_CHECK_HIP(enqueue_step(j + 1));

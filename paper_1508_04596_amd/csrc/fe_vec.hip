@@ -63,6 +63,15 @@ __device__ __forceinline__ void block_sums(double (&acc)[KMAX], int k, double *p
 constexpr int DGS_GROUP = 32;
 #define DGS_WAVES __attribute__((amdgpu_waves_per_eu(1, 4)))
 
+// A scalar for the host, in pinned memory: the step's few products go there from the
+// kernels that form them.  Copied by the runtime they took a launch more per Krylov step
+// (2.5 us and a gap, and up to 20 us of the host's time).  The host reads it after an
+// event or the stream is waited for.
+__device__ __forceinline__ void to_host(double *p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Reduction column of accumulator q of a group of nc columns from c0.
 __device__ __forceinline__ int dgs_out(int q, int nc, bool w, int J, int c0)
 {
@@ -138,7 +147,8 @@ __global__ __launch_bounds__(RED_THREADS) DGS_WAVES void k_dgs_update(const doub
                                                             double *__restrict__ w, int64_t ld, int J,
                                                             int c0, int64_t n,
                                                             double *__restrict__ hb,
-                                                            double *__restrict__ partial)
+                                                            double *__restrict__ partial,
+                                                            double *host)
 {
     __shared__ double cs[NC > 0 ? NC : 1], cp[NC > 0 ? NC : 1], coef[3];
     if ((int)threadIdx.x < NC) {
@@ -162,6 +172,11 @@ __global__ __launch_bounds__(RED_THREADS) DGS_WAVES void k_dgs_update(const doub
                 hb[2 * J + 3] = sig;
                 hb[2 * J + 4] = h;
                 hb[2 * J + 5] = om;
+                if (host) {
+                    to_host(host + 2 * J + 3, sig);
+                    to_host(host + 2 * J + 4, h);
+                    to_host(host + 2 * J + 5, om);
+                }
             }
         }
     }
@@ -198,10 +213,11 @@ __global__ __launch_bounds__(RED_THREADS) DGS_WAVES void k_dgs_update(const doub
 __global__ __launch_bounds__(256) void k_reduce(const double *__restrict__ partial,
                                                 double *__restrict__ out,
                                                 const double *__restrict__ add, int k, int sqrt_last,
-                                                int nparts)
+                                                int nparts, double *host)
 {
     // one workgroup per output; nparts (<= RED_BLOCKS) partials, summed in a
-    // fixed tree: thread t adds partials t, t + 256, ... in order, then the waves
+    // fixed tree: thread t adds partials t, t + 256, ... in order, then the waves.
+    // host: if not null, pinned memory that receives the outputs as well
     __shared__ double red[4];
     const int j = blockIdx.x;
     const double *p = partial + (int64_t)j * RED_BLOCKS;
@@ -215,6 +231,7 @@ __global__ __launch_bounds__(256) void k_reduce(const double *__restrict__ parti
         if (add) t += add[j];
         if (sqrt_last && j == k - 1) t = sqrt(t);
         out[j] = t;
+        if (host) to_host(host + j, t);
     }
 }
 
@@ -360,11 +377,11 @@ __global__ void k_xpld(int64_t n, const double *__restrict__ x, double lam,
     if (i < n) y[i] = x[i] + lam * d[i];
 }
 
-__global__ void k_scale_div(int64_t n, const double *__restrict__ x, const double *__restrict__ s,
+__global__ void k_scale_div(int64_t n, const double *__restrict__ x, double s,
                             double *__restrict__ y)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const double inv = 1.0 / s[0];
+    const double inv = 1.0 / s;
     if (i < n) y[i] = x[i] * inv;
 }
 
@@ -463,10 +480,10 @@ template hipError_t launch_block_apply<float, double, float>(const float *, cons
                                                              hipStream_t);
 
 hipError_t launch_reduce(const double *partial, int k, double *out, const double *add,
-                         bool sqrt_last, hipStream_t st, int nparts)
+                         bool sqrt_last, hipStream_t st, int nparts, double *host)
 {
     hipLaunchKernelGGL(k_reduce, dim3(k), dim3(256), 0, st, partial, out, add, k, sqrt_last ? 1 : 0,
-                       nparts);
+                       nparts, host);
     return hipGetLastError();
 }
 
@@ -522,19 +539,19 @@ static hipError_t dgs_dots(bool w, const double *V, int64_t ld, int J, int64_t n
 }
 
 hipError_t launch_dgs_step(double *V, int64_t ld, int J, int64_t n, double *hb, double *partial,
-                           hipStream_t st)
+                           double *host, hipStream_t st)
 {
     if (J < 0 || J > 63) return hipErrorInvalidValue;
     const int np = red_blocks(n);
     hipError_t e;
     if ((e = dgs_dots(true, V, ld, J, n, partial, st)) != hipSuccess) return e;
-    if ((e = launch_reduce(partial, 2 * J + 3, hb, nullptr, false, st, np)) != hipSuccess) return e;
+    if ((e = launch_reduce(partial, 2 * J + 3, hb, nullptr, false, st, np, host)) != hipSuccess) return e;
     double *c = V + (int64_t)J * ld, *w = V + (int64_t)(J + 1) * ld;
     const dim3 g(np), b(RED_THREADS);
     int c0 = 0;
     if (J > DGS_GROUP) {  // the first DGS_GROUP columns in place, the rest with the final step
         hipLaunchKernelGGL((k_dgs_update<DGS_GROUP, false>), g, b, 0, st, (const double *)V, c, w, ld,
-                           J, 0, n, hb, partial);
+                           J, 0, n, hb, partial, host);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         c0 = DGS_GROUP;
     }
@@ -542,7 +559,7 @@ hipError_t launch_dgs_step(double *V, int64_t ld, int J, int64_t n, double *hb, 
 #define FE_UF(K)                                                                              \
     case K:                                                                                   \
         hipLaunchKernelGGL((k_dgs_update<K, true>), g, b, 0, st, (const double *)V, c, w, ld, J, \
-                           c0, n, hb, partial);                                              \
+                           c0, n, hb, partial, host);                                        \
         break;
         FE_UF(0)
         FE_NC_CASES(FE_UF)
@@ -551,16 +568,17 @@ hipError_t launch_dgs_step(double *V, int64_t ld, int J, int64_t n, double *hb, 
         return hipErrorInvalidValue;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_reduce(partial, 1, hb + 2 * J + 8, nullptr, false, st, np);
+    return launch_reduce(partial, 1, hb + 2 * J + 8, nullptr, false, st, np,
+                         host ? host + 2 * J + 8 : nullptr);
 }
 
 hipError_t launch_dgs_final(const double *V, int64_t ld, int J, int64_t n, double *hb,
-                            double *partial, hipStream_t st)
+                            double *partial, double *host, hipStream_t st)
 {
     if (J < 1 || J > 64) return hipErrorInvalidValue;
     hipError_t e;
     if ((e = dgs_dots(false, V, ld, J, n, partial, st)) != hipSuccess) return e;
-    return launch_reduce(partial, J + 1, hb, nullptr, false, st, red_blocks(n));
+    return launch_reduce(partial, J + 1, hb, nullptr, false, st, red_blocks(n), host);
 }
 
 hipError_t launch_norm2_partial(const double *a, int64_t n, double *partial, hipStream_t st)
@@ -582,7 +600,7 @@ hipError_t launch_xpld(int64_t n, const double *x, double lam, const double *d, 
     return hipGetLastError();
 }
 
-hipError_t launch_scale_div(int64_t n, const double *x, const double *s, double *y, hipStream_t st)
+hipError_t launch_scale_div(int64_t n, const double *x, double s, double *y, hipStream_t st)
 {
     hipLaunchKernelGGL(k_scale_div, dim3(nblk(n)), dim3(256), 0, st, n, x, s, y);
     return hipGetLastError();
