@@ -11,11 +11,12 @@
 // elements that hold both, and K psi = b is solved by Jacobi-preconditioned
 // conjugate gradients with every scalar kept on the device.
 //
-// Two launches per iteration.  The first forms the direction p = z + beta p where
-// K p needs it: a workgroup stages p of a plane of its tile and the rim in LDS, whose
-// sums over the nine neighbours of a node serve three planes.  The second updates
-// the residual, and x every other time.  The partial sums of a pass are added by
-// every workgroup of the next, in the same order, in place of a launch of its own.
+// Two launches per iteration, or one on small grids (k_cg below; CG_ONE).  Of two, the
+// first forms the direction p = z + beta p where K p needs it: a workgroup stages p of a
+// plane of its tile and the rim in LDS, whose sums over the nine neighbours of a node
+// serve three planes.  The second updates the residual, and x every other time.  The
+// partial sums of a pass are added by every workgroup of the next, in the same order, in
+// place of a launch of its own.
 // Bound: up to about 10^6 nodes the latency of a pass (5.5 us: partial sums, then
 // one plane after the other), above it memory (10 vectors per iteration; 160x160x320
 // elements at about 3.9 TB/s).  Forward and transpose at 64x64x128, 24 iterations
@@ -43,9 +44,9 @@ __device__ __forceinline__ void node_ijk(const FGeo &g, int64_t n, int &I, int &
     K = (int)(r / (g.ny + 1));
 }
 
-// block partial sums: out_j[blockIdx.x], j < NV <= 2
+// block partial sums: out[j * RED_BLOCKS + blockIdx.x], j < NV
 template <int NV>
-__device__ __forceinline__ void block_partials(const double *v, double *out0, double *out1)
+__device__ __forceinline__ void block_partials(const double *v, double *out)
 {
     __shared__ double red[NV][RED_THREADS / 64];
 #pragma unroll
@@ -58,7 +59,7 @@ __device__ __forceinline__ void block_partials(const double *v, double *out0, do
     if (threadIdx.x < NV) {
         double s = 0.0;
         for (int w = 0; w < RED_THREADS / 64; ++w) s += red[threadIdx.x][w];
-        (threadIdx.x == 0 ? out0 : out1)[blockIdx.x] = s;
+        out[threadIdx.x * RED_BLOCKS + blockIdx.x] = s;
     }
 }
 
@@ -162,13 +163,38 @@ __device__ __forceinline__ double total(const double *__restrict__ partial, int 
     return v;
 }
 
+// Sums of a staged plane (u: its tile with the rim) over a node itself, its edge
+// neighbours and its corner neighbours, each weighted by the elements along x and y in
+// common.
+struct Sums {
+    double a0, a1, a2, p;
+};
+__device__ __forceinline__ Sums plane_sums(const double *u, const Column &c, const CgTiling &t)
+{
+    const int sx = t.wx + 2;
+    const int at = ((int)threadIdx.x / t.wx + 1) * sx + (int)threadIdx.x % t.wx + 1;
+    const double *P = u + (c.in ? at : sx + 1);
+    Sums s;
+    s.p = P[0];
+    s.a0 = c.cx * c.cy * s.p;
+    s.a1 = c.cy * (P[-1] + P[1]) + c.cx * (P[-sx] + P[sx]);
+    s.a2 = (P[-sx - 1] + P[-sx + 1]) + (P[sx - 1] + P[sx + 1]);
+    return s;
+}
+// (K u) of a node with cz elements along z from its three planes' sums
+__device__ __forceinline__ double stencil(const FGeo &g, double cz, const Sums &lo, const Sums &me,
+                                          const Sums &hi)
+{
+    return cz * (g.E[0] * me.a0 + g.E[1] * me.a1 + g.E[2] * me.a2) + g.E[1] * (lo.a0 + hi.a0) +
+           g.E[2] * (lo.a1 + hi.a1) + g.E[3] * (lo.a2 + hi.a2);
+}
+
 // CG start from x = 0: z = D^-1 b (D = E0 times the node's elements); partials of
 // <r, z> and <r, r>.
 __global__ __launch_bounds__(RED_THREADS) void k_cg_init(FGeo g, CgTiling t, double iE0,
                                                          const double *__restrict__ b,
                                                          double *__restrict__ x,
-                                                         double *__restrict__ z, double *prz,
-                                                         double *prr)
+                                                         double *__restrict__ z, double *prz)
 {
     double v[2] = {0.0, 0.0};
     const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
@@ -186,7 +212,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_init(FGeo g, CgTiling t, dou
             v[1] += rn * rn;
         }
     }
-    block_partials<2>(v, prz, prr);
+    block_partials<2>(v, prz);
 }
 
 // p = z + beta p_old (z in the first iteration), y = K p, partials of <p, y>.
@@ -202,7 +228,6 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
                                                           double *__restrict__ y, double *ppy)
 {
     __shared__ double w[2][TILE_HALO];  // p of a plane of the tile and its rim, ring of two
-    const double E0 = g.E[0], E1 = g.E[1], E2 = g.E[2], E3 = g.E[3];
     const int sx = t.wx + 2, halo = sx * (t.wy + 2);
     constexpr int NL = (TILE_HALO + RED_THREADS - 1) / RED_THREADS;
     double v = 0.0, beta = 0.0;
@@ -238,22 +263,6 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
                 if (e < halo) w[b][e] = ok[q] ? (FIRST ? zr[q] : fma(beta, pr[q], zr[q])) : 0.0;
             }
         };
-        // in-plane sums over the node itself, its edge neighbours and its corner
-        // neighbours, each weighted by the elements along x and y in common
-        struct Sums {
-            double a0, a1, a2, p;
-        };
-        const int me0 = ((int)threadIdx.x / t.wx + 1) * sx + (int)threadIdx.x % t.wx + 1;
-        const int m = c.in ? me0 : sx + 1;
-        auto sums = [&](int b) {
-            const double *P = w[b] + m;
-            Sums s;
-            s.p = P[0];
-            s.a0 = c.cx * c.cy * s.p;
-            s.a1 = c.cy * (P[-1] + P[1]) + c.cx * (P[-sx] + P[sx]);
-            s.a2 = (P[-sx - 1] + P[-sx + 1]) + (P[sx - 1] + P[sx + 1]);
-            return s;
-        };
         const Sums none = {0.0, 0.0, 0.0, 0.0};
         const int Ka = max(c.K0 - 1, 0), Kb = min(c.K1, g.nz);  // planes to stage
         load(Ka);
@@ -273,13 +282,12 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
                 stage(K & 1);
                 if (K < Kb) load(K + 1);
                 __syncthreads();
-                hi = sums(K & 1);
+                hi = plane_sums(w[K & 1], c, t);
             }
             const int Ko = K - 1;
             if (c.in && Ko >= c.K0 && Ko < c.K1) {
                 const double cz = (Ko > 0) + (Ko < g.nz);
-                const double yn = cz * (E0 * me.a0 + E1 * me.a1 + E2 * me.a2) +
-                                  E1 * (lo.a0 + hi.a0) + E2 * (lo.a1 + hi.a1) + E3 * (lo.a2 + hi.a2);
+                const double yn = stencil(g, cz, lo, me, hi);
                 const int64_t n = c.n + c.plane * Ko;
                 p[n] = me.p;
                 y[n] = yn;
@@ -289,13 +297,13 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
             me = hi;
         }
     }
-    block_partials<1>(&v, ppy, nullptr);
+    block_partials<1>(&v, ppy);
 }
 
 // alpha = rz / <p, y>; r -= alpha y, kept as z = D^-1 r; partials of <r, z> and
 // <r, r>.  x is updated every other iteration (X), with both directions at hand:
 // x += alpha_old p_old + alpha p, alpha_old as the iteration before left it in
-// sc[5] (both = 0: x += alpha p).  A zero right-hand side leaves x = 0.
+// sc[2] (both = 0: x += alpha p).  A zero right-hand side leaves x = 0.
 template <bool X>
 __global__ __launch_bounds__(RED_THREADS) void k_cg_step(FGeo g, CgTiling t, int nparts, double iE0,
                                                          const double *__restrict__ ppy, double *sc,
@@ -304,13 +312,12 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_step(FGeo g, CgTiling t, int
                                                          const double *__restrict__ p,
                                                          const double *__restrict__ y,
                                                          double *__restrict__ x,
-                                                         double *__restrict__ z, double *prz,
-                                                         double *prr)
+                                                         double *__restrict__ z, double *prz)
 {
     const double py = total(ppy, nparts), rz = sc[cur];
     const double alpha = rz == 0.0 && py == 0.0 ? 0.0 : rz / py;
-    const double before = X && both ? sc[5] : 0.0;
-    if (!X && blockIdx.x == 0 && threadIdx.x == 0) sc[5] = alpha;
+    const double before = X && both ? sc[2] : 0.0;
+    if (!X && blockIdx.x == 0 && threadIdx.x == 0) sc[2] = alpha;
     double v[2] = {0.0, 0.0};
     const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
     const int t1 = tile_begin(t, lb + 1);
@@ -334,7 +341,168 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_step(FGeo g, CgTiling t, int
             v[1] += rn * rn;
         }
     }
-    block_partials<2>(v, prz, prr);
+    block_partials<2>(v, prz);
+}
+
+// Sums of the nparts block partials of two quantities, the same in every workgroup.
+__device__ __forceinline__ void totals(const double *__restrict__ partial, int nparts, double &a,
+                                       double &b)
+{
+    __shared__ double red[2][RED_THREADS / 64];
+    double s[2] = {0.0, 0.0};
+    for (int q = threadIdx.x; q < nparts; q += RED_THREADS) {
+        s[0] += partial[q];
+        s[1] += partial[RED_BLOCKS + q];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        for (int o = 32; o > 0; o >>= 1) s[j] += __shfl_down(s[j], o, 64);
+        if ((threadIdx.x & 63) == 0) red[j][threadIdx.x >> 6] = s[j];
+    }
+    __syncthreads();
+    a = b = 0.0;
+    for (int w = 0; w < RED_THREADS / 64; ++w) {
+        a += red[0][w];
+        b += red[1][w];
+    }
+}
+
+// Vectors of an iteration: u = D^-1 r (D = E0 times the node's elements), w = K u and
+// s = K p are read with the tile's rim and written to their second buffers, p and x are
+// updated in place.
+struct CgVec {
+    const double *u, *w, *s;
+    double *un, *wn, *sn, *p, *x;
+};
+
+// One iteration in one launch (Chronopoulos and Gear's form of conjugate gradients, for
+// small grids): from the last pass's partials of rz = <r, u> and uw = <u, w>,
+//   beta = rz / rz_old,  alpha = rz / (uw - beta rz / alpha_old),
+//   p = u + beta p,  s = w + beta s,  x += alpha p,  u -= alpha D^-1 s,  w = K u,
+// and the partials of the new rz, uw and <r, r> (out).  rz and alpha are kept in
+// sc[2 cur], sc[2 cur + 1] for the next.  INIT: u = D^-1 b (v.u = b), x = 0.
+// fresh: the first iteration, s = p = 0 are not read.  x is updated every other
+// iteration, with both directions at hand: xmode 0 no, 1 x += alpha p, 2 x +=
+// alpha_old p_old + alpha p.  A zero right-hand side leaves x = 0.
+template <bool INIT>
+__global__ __launch_bounds__(RED_THREADS) void k_cg(FGeo g, CgTiling t, int nparts, double iE0,
+                                                    const double *__restrict__ partial, double *sc,
+                                                    int cur, int fresh, int xmode, CgVec vec,
+                                                    double *out)
+{
+    __shared__ double P2[2][TILE_HALO];  // u of a plane of the tile and its rim, ring of two
+    const double E0 = g.E[0];
+    const int sx = t.wx + 2, halo = sx * (t.wy + 2);
+    constexpr int NL = (TILE_HALO + RED_THREADS - 1) / RED_THREADS;
+    const double *__restrict__ u = vec.u;
+    const double *__restrict__ w = vec.w;
+    const double *__restrict__ s = vec.s;
+    double v[3] = {0.0, 0.0, 0.0};
+    double alpha = 0.0, beta = 0.0, before = 0.0;
+    bool first = true;
+    const int lb = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    const int t1 = tile_begin(t, lb + 1);
+    for (int tile = tile_begin(t, lb); tile < t1; ++tile) {
+        const Column c = column(g, t, tile);
+        // this thread's values of the rimmed plane: in the grid, in the tile itself
+        // (those it also updates), elements along x and y
+        int64_t off[NL];
+        bool ok[NL], mine[NL];
+        double cxy[NL], id[NL];
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            const int e = (int)threadIdx.x + q * RED_THREADS, hy = e / sx, hx = e - hy * sx;
+            const int I = c.I0 + hx - 1, J = c.J0 + hy - 1;
+            ok[q] = e < halo && I >= 0 && I <= g.nx && J >= 0 && J <= g.ny;
+            mine[q] = ok[q] && hx >= 1 && hx <= t.wx && hy >= 1 && hy <= t.wy;
+            off[q] = ok[q] ? I + (int64_t)(g.nx + 1) * J : 0;
+            cxy[q] = ((I > 0) + (I < g.nx)) * ((J > 0) + (J < g.ny));
+            id[q] = ok[q] ? iE0 / cxy[q] : 0.0;
+        }
+        double ur[NL], wr[NL], sr[NL], pr[NL], xr[NL];
+        auto load = [&](int K) {
+            const int64_t b = c.plane * K;
+            const bool own = K >= c.K0 && K < c.K1;
+#pragma unroll
+            for (int q = 0; q < NL; ++q)
+                if (q * RED_THREADS < halo) {
+                    ur[q] = u[b + off[q]];
+                    if (INIT) continue;
+                    wr[q] = w[b + off[q]];
+                    sr[q] = fresh ? 0.0 : s[b + off[q]];
+                    pr[q] = own && mine[q] && !fresh ? vec.p[b + off[q]] : 0.0;
+                    xr[q] = own && mine[q] && xmode ? vec.x[b + off[q]] : 0.0;
+                }
+        };
+        auto stage = [&](int K) {
+            const int64_t b = c.plane * K;
+            const bool own = K >= c.K0 && K < c.K1;
+            const bool inner = K > 0 && K < g.nz;  // two elements along z
+#pragma unroll
+            for (int q = 0; q < NL; ++q) {
+                const int e = (int)threadIdx.x + q * RED_THREADS;
+                if (e >= halo) continue;
+                const double di = inner ? 0.5 * id[q] : id[q];
+                const double sn = INIT ? 0.0 : fma(beta, sr[q], wr[q]);
+                const double un = ok[q] ? (INIT ? ur[q] * di : ur[q] - alpha * sn * di) : 0.0;
+                P2[K & 1][e] = un;
+                if (!(own && mine[q])) continue;
+                const int64_t n = b + off[q];
+                vec.un[n] = un;
+                if (INIT) {
+                    vec.x[n] = 0.0;
+                } else {
+                    const double pn = fma(beta, pr[q], ur[q]);
+                    vec.sn[n] = sn;
+                    vec.p[n] = pn;
+                    if (xmode) vec.x[n] = fma(alpha, pn, xmode == 2 ? fma(before, pr[q], xr[q]) : xr[q]);
+                }
+                const double rn = un * (E0 * cxy[q] * (inner ? 2.0 : 1.0));
+                v[0] += rn * un;
+                v[2] += rn * rn;
+            }
+        };
+        const Sums none = {0.0, 0.0, 0.0, 0.0};
+        const int Ka = max(c.K0 - 1, 0), Kb = min(c.K1, g.nz);  // planes to stage
+        load(Ka);
+        if (!first) {
+            __syncthreads();  // the last tile's planes have been read
+        } else if (!INIT) {
+            double rz, uw;
+            totals(partial, nparts, rz, uw);
+            const double old = fresh ? 0.0 : sc[2 - 2 * cur];
+            before = fresh ? 0.0 : sc[3 - 2 * cur];
+            beta = old > 0.0 ? rz / old : 0.0;
+            const double d = beta == 0.0 ? uw : uw - beta * rz / before;
+            alpha = rz == 0.0 && uw == 0.0 ? 0.0 : rz / d;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                sc[2 * cur] = rz;
+                sc[2 * cur + 1] = alpha;
+            }
+        }
+        first = false;
+        Sums lo = none, me = none;
+        for (int K = Ka; K <= Kb + 1; ++K) {
+            // plane K joins; plane K - 1 is complete
+            Sums hi = none;
+            if (K <= Kb) {
+                stage(K);
+                if (K < Kb) load(K + 1);
+                __syncthreads();
+                hi = plane_sums(P2[K & 1], c, t);
+            }
+            const int Ko = K - 1;
+            if (c.in && Ko >= c.K0 && Ko < c.K1) {
+                const double cz = (Ko > 0) + (Ko < g.nz);
+                const double wn = stencil(g, cz, lo, me, hi);
+                vec.wn[c.n + c.plane * Ko] = wn;
+                v[1] += me.p * wn;
+            }
+            lo = me;
+            me = hi;
+        }
+    }
+    block_partials<3>(v, out);
 }
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -343,6 +511,11 @@ inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // ---- host side --------------------------------------------------------------------
 
+// Largest grid (nodes) whose iteration is one launch: up to there a pass's latency
+// bounds, above it the rims of the three vectors it stages cost more than the launch (us
+// per solve, two launches / one: 16^3 350 268, 32x32x64 355 290, 48x48x96 387 344, 64^3
+// 396 375, 64x64x96 425 414, 64x64x128 484 503, 96^3 628 943).
+constexpr int64_t CG_ONE = 300000;
 
 hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
 {
@@ -362,7 +535,9 @@ hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
     if (e == hipSuccess) e = hipMalloc(&f->r, nb);
     if (e == hipSuccess) e = hipMalloc(&f->p, nb);
     if (e == hipSuccess) e = hipMalloc(&f->y, nb);
-    if (e == hipSuccess) e = hipMalloc(&f->partial, sizeof(double) * 3 * RED_BLOCKS);
+    for (double **q : {&f->r2, &f->y2, &f->s2})
+        if (e == hipSuccess && f->nn <= CG_ONE) e = hipMalloc(q, nb);
+    if (e == hipSuccess) e = hipMalloc(&f->partial, sizeof(double) * 6 * RED_BLOCKS);
     if (e == hipSuccess) e = hipMalloc(&f->sc, sizeof(double) * 8);
     if (e == hipSuccess) e = hipHostMalloc(&f->hsc, sizeof(double) * 8);
     return e;
@@ -370,7 +545,7 @@ hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
 
 void filter_free(Filter *f)
 {
-    for (double *q : {f->b, f->x, f->r, f->p, f->y, f->partial, f->sc})
+    for (double *q : {f->b, f->x, f->r, f->p, f->y, f->r2, f->y2, f->s2, f->partial, f->sc})
         if (q) (void)hipFree(q);
     if (f->hsc) (void)hipHostFree(f->hsc);
 }
@@ -380,35 +555,81 @@ void filter_free(Filter *f)
 // idle and one plane per tile doubles what a tile stages (us per solve at 1 / 2 / 4 /
 // 6 / 8 planes, 24 iterations: 32x32x64 340 294 372 379 393; 64x64x128 591 539 481
 // 469 514; 96^3 706 656 669 568 631; 160x160x320 5503 4900 4694 4655 4585).
-static CgTiling cg_tiling(const FGeo &g)
+// One launch per iteration (small grids): as few planes as keep all tiles resident, two
+// per CU (40x40x80 with 648 tiles of one plane: 453, with 324 of two: 333).
+static CgTiling cg_tiling(const FGeo &g, bool one)
 {
     CgTiling t;
     t.nx = (g.nx + TILE_W) / TILE_W;
     t.wx = (g.nx + t.nx) / t.nx;
     t.wy = std::min(RED_THREADS / t.wx, g.ny + 1);
     t.ny = (g.ny + t.wy) / t.wy;
-    const int64_t cz = (int64_t)t.nx * t.ny * (g.nz + 1) / 400;
-    t.cz = (int)std::min<int64_t>(std::max<int64_t>(2, std::min<int64_t>(cz, 8)), g.nz + 1);
+    const int64_t planes = (int64_t)t.nx * t.ny * (g.nz + 1);
+    const int64_t cz = one ? (planes + 511) / 512 : std::max<int64_t>(2, planes / 400);
+    t.cz = (int)std::min<int64_t>(std::min<int64_t>(cz, 8), g.nz + 1);
     t.tiles = t.nx * t.ny * ((g.nz + t.cz) / t.cz);
     return t;
 }
 
-// psi = K^-1 b (b, psi: the filter's own node buffers b and x; b is overwritten);
-// returns FE_OK, FE_NOT_CONVERGED or an error
-int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
+// After iteration it: FE_NOT_CONVERGED to go on.  sc[4] receives <r, r> (prr: its
+// partials); sc[5] holds its first value.
+static int converged(Filter *f, const double *prr, int nb, int it, double rtol, hipStream_t st)
+{
+    FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 4, nullptr, false, st, nb));
+    FE_CHECK_HIP(hipMemcpyAsync(f->hsc + 4, f->sc + 4, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+    FE_CHECK_HIP(hipStreamSynchronize(st));
+    const double rr = f->hsc[4], rr0 = f->hsc[5];
+    if (rr0 == 0.0) return FE_OK;
+    if (!(rr0 > 0.0)) return FE_ENAN;
+    f->last_its = it;
+    if (!std::isfinite(rr)) return FE_ENAN;
+    return rr <= rtol * rtol * rr0 ? FE_OK : FE_NOT_CONVERGED;
+}
+
+static int solve_one(Filter *f, hipStream_t st, double rtol, int max_its)
 {
     const FGeo &g = f->g;
-    const CgTiling t = cg_tiling(g);
+    const CgTiling t = cg_tiling(g, true);
     const int nb = std::min(t.tiles, RED_BLOCKS);
     const dim3 gb(nb), gt(RED_THREADS);
-    double *ppy = f->partial, *prz = f->partial + RED_BLOCKS, *prr = f->partial + 2 * RED_BLOCKS;
+    // partials of rz, uw and rr, two sets in turn; sc: rz and alpha of the last two
+    // iterations, then rr and its first value
+    double *part[2] = {f->partial, f->partial + 3 * RED_BLOCKS};
     const double iE0 = 1.0 / g.E[0];
-    hipLaunchKernelGGL(k_cg_init, gb, gt, 0, st, g, t, iE0, (const double *)f->b, f->x, f->r, prz,
-                       prr);
+    CgVec v = {f->b, nullptr, nullptr, f->r, f->y, nullptr, f->p, f->x};
+    hipLaunchKernelGGL(k_cg<true>, gb, gt, 0, st, g, t, nb, iE0, (const double *)nullptr, f->sc, 0, 1,
+                       0, v, part[0]);
     FE_CHECK_HIP(hipGetLastError());
-    // sc[0], sc[1]: rz of the last two iterations; sc[3] = rr, sc[4] = its first value;
-    // sc[5]: alpha of the iteration before
-    FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 4, nullptr, false, st, nb));
+    FE_CHECK_HIP(launch_reduce(part[0] + 2 * RED_BLOCKS, 1, f->sc + 5, nullptr, false, st, nb));
+    v = {f->r, f->y, f->s2, f->r2, f->y2, f->b, f->p, f->x};
+    f->last_its = 0;
+    for (int it = 1; it <= max_its; ++it) {
+        const int cur = it & 1;
+        hipLaunchKernelGGL(k_cg<false>, gb, gt, 0, st, g, t, nb, iE0, (const double *)part[1 - cur],
+                           f->sc, cur, it == 1, it % 2 == 0 ? 2 : it == max_its ? 1 : 0, v, part[cur]);
+        FE_CHECK_HIP(hipGetLastError());
+        v = {v.un, v.wn, v.sn, const_cast<double *>(v.u), const_cast<double *>(v.w),
+             const_cast<double *>(v.s), f->p, f->x};
+        if (it % 8 == 0 || it == max_its) {
+            const int rc = converged(f, part[cur] + 2 * RED_BLOCKS, nb, it, rtol, st);
+            if (rc != FE_NOT_CONVERGED) return rc;
+        }
+    }
+    return FE_NOT_CONVERGED;
+}
+
+static int solve_two(Filter *f, hipStream_t st, double rtol, int max_its)
+{
+    const FGeo &g = f->g;
+    const CgTiling t = cg_tiling(g, false);
+    const int nb = std::min(t.tiles, RED_BLOCKS);
+    const dim3 gb(nb), gt(RED_THREADS);
+    double *ppy = f->partial, *prz = f->partial + RED_BLOCKS, *prr = prz + RED_BLOCKS;
+    const double iE0 = 1.0 / g.E[0];
+    hipLaunchKernelGGL(k_cg_init, gb, gt, 0, st, g, t, iE0, (const double *)f->b, f->x, f->r, prz);
+    FE_CHECK_HIP(hipGetLastError());
+    // sc[0], sc[1]: rz of the last two iterations; sc[2]: alpha of the one before
+    FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 5, nullptr, false, st, nb));
     double *pn = f->p, *po = f->b;
     int cur = 0;
     f->last_its = 0;
@@ -422,28 +643,27 @@ int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
         if (it % 2 == 0 || it == max_its)
             hipLaunchKernelGGL(k_cg_step<true>, gb, gt, 0, st, g, t, nb, iE0, (const double *)ppy,
                                f->sc, cur, it % 2 == 0, (const double *)po, (const double *)pn,
-                               (const double *)f->y, f->x, f->r, prz, prr);
+                               (const double *)f->y, f->x, f->r, prz);
         else
             hipLaunchKernelGGL(k_cg_step<false>, gb, gt, 0, st, g, t, nb, iE0, (const double *)ppy,
                                f->sc, cur, 0, (const double *)po, (const double *)pn,
-                               (const double *)f->y, f->x, f->r, prz, prr);
+                               (const double *)f->y, f->x, f->r, prz);
         FE_CHECK_HIP(hipGetLastError());
         cur = 1 - cur;
         std::swap(pn, po);
         if (it % 8 == 0 || it == max_its) {
-            FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 3, nullptr, false, st, nb));
-            FE_CHECK_HIP(hipMemcpyAsync(f->hsc + 3, f->sc + 3, 2 * sizeof(double),
-                                        hipMemcpyDeviceToHost, st));
-            FE_CHECK_HIP(hipStreamSynchronize(st));
-            const double rr = f->hsc[3], rr0 = f->hsc[4];
-            if (rr0 == 0.0) return FE_OK;
-            if (!(rr0 > 0.0)) return FE_ENAN;
-            f->last_its = it;
-            if (!std::isfinite(rr)) return FE_ENAN;
-            if (rr <= rtol * rtol * rr0) return FE_OK;
+            const int rc = converged(f, prr, nb, it, rtol, st);
+            if (rc != FE_NOT_CONVERGED) return rc;
         }
     }
     return FE_NOT_CONVERGED;
+}
+
+// psi = K^-1 b (b, psi: the filter's own node buffers b and x; b is overwritten);
+// returns FE_OK, FE_NOT_CONVERGED or an error
+int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
+{
+    return f->nn <= CG_ONE ? solve_one(f, st, rtol, max_its) : solve_two(f, st, rtol, max_its);
 }
 
 hipError_t filter_load(Filter *f, const double *gamma, double scale, hipStream_t st)

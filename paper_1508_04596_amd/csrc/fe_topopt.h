@@ -16,7 +16,8 @@ struct Filter {
     int64_t nn = 0, ne = 0;
     double load = 0.0;  // h^3 / 8
     double *b = nullptr, *x = nullptr, *r = nullptr, *p = nullptr, *y = nullptr;
-    double *partial = nullptr, *sc = nullptr;  // sc: rz[0], rz[1], pAp, rr, rr0
+    double *r2 = nullptr, *y2 = nullptr, *s2 = nullptr;  // second buffers of the iteration
+    double *partial = nullptr, *sc = nullptr;  // sc: rz, alpha of two iterations, rr, rr0
     double *hsc = nullptr;                     // pinned host scalars
     int last_its = 0;
 };
