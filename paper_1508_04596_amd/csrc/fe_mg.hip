@@ -398,8 +398,8 @@ __global__ __launch_bounds__(576) void k_stencil_smooth(int nx, int ny, int nz, 
 // The values are those of k_smooth0_cast / k_smooth, k_coarse_apply_sum and
 // k_prolong_add.  A small level's launch costs 3 to 6 us whatever it does; these save
 // one (SW_COARSE: two) each for 2 to 5 us of gathers.  With the gap between launches,
-// V-cycle of 3 levels, kernels alone: FP32 16^3 first sweep 3.6 + 7.0 -> 10.2 us, post
-// sweep 3.4 + 7.0 -> 9.1, above a 4^3 coarsest level 2.6 + 3.4 + 5.6 -> 8.7; FP64
+// V-cycle of 3 levels, kernels alone: FP32 16^3 first sweep 3.6 + 7.0 -> 9.5 us, post
+// sweep 3.4 + 7.0 -> 8.1, above a 4^3 coarsest level 2.6 + 3.4 + 5.6 -> 8.4; FP64
 // 16x16x32 post sweep 4.1 + 15 -> 17.7, above 4x4x8 2.6 + 3.5 + 9.2 -> 12.6.  13
 // launches -> 9.  What bounds them is the stencil's read (16x16x32 in FP64: 51 MB) and,
 // below 10^4 nodes, the chain of gather, stencil, sum and block product.
@@ -444,6 +444,73 @@ __global__ __launch_bounds__(576) void k_stencil_sweep(int nx, int ny, int nz,
         const int d = 3 * p + c, g = g0 + gg;
         return S[(TR ? (26 - d) * 25 + f * NF + g : d * 25 + g * NF + f) * (int64_t)nn + M3[c]];
     };
+    // Loads return in the order they are issued: first what the iterate needs, then the
+    // nodal blocks and the stencil (FP32, 16^3: post sweep 9.0 -> 8.1 us).
+    constexpr int NG = (9 * RUN + 575) / 576;
+    struct Node {
+        int M, f;
+        bool own;  // one of this workgroup's nodes
+    };
+    auto gathered = [&](int m) {
+        const int q = min(tid + 576 * m, 9 * RUN - 1);
+        const int run = q / RUN, e = q - run * RUN, en = e / NF;
+        const int M0 = n0 - 1 + en + (run % 3 - 1) * (nx + 1) + (run / 3 - 1) * sxy;
+        Node o;
+        o.f = e - NF * en;
+        o.M = min(max(M0, 0), nn - 1);  // (not read by any lane where clamped)
+        o.own = run == 4 && M0 >= n0 && M0 < n0 + SN && M0 < nn;
+        return o;
+    };
+    struct Corners {
+        int cn[8];
+        int oi, oj, ok;
+    };
+    auto corners = [&](int M) {
+        Corners o;
+        const int fk = M / sxy, fr = M - fk * sxy, fj = fr / (nx + 1), fi = fr - fj * (nx + 1);
+        o.oi = fi & 1;
+        o.oj = fj & 1;
+        o.ok = fk & 1;
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            o.cn[c] = ((fi >> 1) + (c & 1) * o.oi) +
+                      (in.ncx + 1) * (((fj >> 1) + ((c >> 1) & 1) * o.oj) +
+                                      (in.ncy + 1) * ((fk >> 1) + (c >> 2) * o.ok));
+        return o;
+    };
+    T ga[NG][8], gb[NG][NF];  // SW_FIRST: D's row and b; else the coarse corners and x
+    uint8_t gm[NG];
+    auto gather = [&](int m) {
+        const Node o = gathered(m);
+        if (MODE == SW_FIRST) {
+#pragma unroll
+            for (int c = 0; c < NF; ++c) {
+                ga[m][c] = D[o.M * 25 + (TR ? c * NF + o.f : o.f * NF + c)];
+                gb[m][c] = in.v ? (T)in.v[NF * o.M + c] : b[NF * o.M + c];
+            }
+        } else {
+            gm[m] = in.fmask[o.M];
+            gb[m][0] = in.x[NF * o.M + o.f];
+            if (MODE == SW_PROLONG) {
+                const Corners k8 = corners(o.M);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) ga[m][c] = in.xc[NF * k8.cn[c] + o.f];
+            }
+        }
+    };
+    if (AHEAD) {
+#pragma unroll
+        for (int m = 0; m < NG; ++m) gather(m);
+    }
+    // the workgroup's nodal blocks, coalesced (entries past nn repeat the last)
+    constexpr int ND = (SN * 25 + 575) / 576;
+    T dv[ND];
+    {
+        const int cnt = min(nn - n0, SN) * 25;
+        const T *src = D + (int64_t)n0 * 25;
+#pragma unroll
+        for (int m = 0; m < ND; ++m) dv[m] = src[min(tid + 576 * m, cnt - 1)];
+    }
     T a[3][3 * NF];
     if (AHEAD) {
 #pragma unroll
@@ -451,16 +518,6 @@ __global__ __launch_bounds__(576) void k_stencil_sweep(int nx, int ny, int nz,
             if (gg < ng)
 #pragma unroll
                 for (int q = 0; q < 3 * NF; ++q) a[gg][q] = entry(gg, q / NF, q % NF);
-    }
-    // the workgroup's nodal blocks, coalesced (entries past nn repeat the last)
-    {
-        const int cnt = min(nn - n0, SN) * 25;
-        const T *src = D + (int64_t)n0 * 25;
-#pragma unroll
-        for (int m = 0; m < (SN * 25 + 575) / 576; ++m) {
-            const int q = tid + 576 * m;
-            if (q < SN * 25) sD[q] = src[q < cnt ? q : cnt - 1];
-        }
     }
     T *xco = reinterpret_cast<T *>(coarse_mem);
     if (MODE == SW_COARSE) {
@@ -475,48 +532,37 @@ __global__ __launch_bounds__(576) void k_stencil_sweep(int nx, int ny, int nz,
         __syncthreads();
     }
 #pragma unroll
-    for (int m = 0; m < (9 * RUN + 575) / 576; ++m) {
+    for (int m = 0; m < NG; ++m) {
         const int q = tid + 576 * m;
-        if (q >= 9 * RUN) break;
-        const int run = q / RUN, e = q - run * RUN, en = e / NF, f = e - NF * en;
-        const int M0 = n0 - 1 + en + (run % 3 - 1) * (nx + 1) + (run / 3 - 1) * sxy;
-        const int M = min(max(M0, 0), nn - 1);  // (not read by any lane where clamped)
+        const Node o = gathered(m);
+        if (!AHEAD) gather(m);
         T x;
         if (MODE == SW_FIRST) {
             T acc = T(0), own = T(0);
 #pragma unroll
             for (int c = 0; c < NF; ++c) {
-                const T bv = in.v ? (T)in.v[NF * M + c] : b[NF * M + c];
-                acc += D[M * 25 + (TR ? c * NF + f : f * NF + c)] * bv;
-                if (c == f) own = bv;
+                acc += ga[m][c] * gb[m][c];
+                if (c == o.f) own = gb[m][c];
             }
             x = omega * acc;
-            if (in.bout && run == 4 && M0 >= n0 && M0 < n0 + SN && M0 < nn) in.bout[NF * M + f] = own;
+            if (in.bout && o.own && q < 9 * RUN) in.bout[NF * o.M + o.f] = own;
         } else {
-            const int fk = M / sxy, fr = M - fk * sxy, fj = fr / (nx + 1), fi = fr - fj * (nx + 1);
-            const int oi = fi & 1, oj = fj & 1, ok = fk & 1;
-            const T wi = oi ? T(0.5) : T(1), wj = oj ? T(0.5) : T(1), wk = ok ? T(0.5) : T(1);
-            const T *xc = MODE == SW_COARSE ? xco : in.xc;
+            const Corners k8 = corners(o.M);
+            const T wi = k8.oi ? T(0.5) : T(1), wj = k8.oj ? T(0.5) : T(1), wk = k8.ok ? T(0.5) : T(1);
             T acc = T(0);
 #pragma unroll
-            for (int cz = 0; cz < 2; ++cz)
-#pragma unroll
-                for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-                    for (int cx = 0; cx < 2; ++cx) {
-                        const bool use = (cz <= ok) && (cy <= oj) && (cx <= oi);
-                        const int cn = ((fi >> 1) + cx * oi) +
-                                       (in.ncx + 1) * (((fj >> 1) + cy * oj) +
-                                                       (in.ncy + 1) * ((fk >> 1) + cz * ok));
-                        const T v = xc[NF * cn + f];
-                        acc += use ? v : T(0);
-                    }
-            const int mk = in.fmask[M];
-            const T xq = in.x[NF * M + f];
-            x = ((mk >> f) & 1) ? xq : xq + wi * wj * wk * acc;
+            for (int c = 0; c < 8; ++c) {
+                const bool use = (c >> 2) <= k8.ok && ((c >> 1) & 1) <= k8.oj && (c & 1) <= k8.oi;
+                const T v = MODE == SW_COARSE ? xco[NF * k8.cn[c] + o.f] : ga[m][c];
+                acc += use ? v : T(0);
+            }
+            x = ((gm[m] >> o.f) & 1) ? gb[m][0] : gb[m][0] + wi * wj * wk * acc;
         }
-        sx[q] = x;
+        if (q < 9 * RUN) sx[q] = x;
     }
+#pragma unroll
+    for (int m = 0; m < ND; ++m)
+        if (tid + 576 * m < SN * 25) sD[tid + 576 * m] = dv[m];
     __syncthreads();
 #pragma unroll
     for (int gg = 0; gg < 3; ++gg) {
