@@ -1,5 +1,5 @@
-"""The density filter's one-launch iteration (grids up to 300,000 nodes): several tiles
-against exact sparse solves; a zero field; a field that is not a number; and the sizes on
+"""The density filter's one-launch iteration (grids up to 300,000 nodes): several tiles,
+also several per workgroup (1x1x9000), against exact sparse solves; a zero field; a field that is not a number; and the sizes on
 both sides of the limit, too large for a sparse factorisation here, by what F must keep
 (constants, and <F u, v> = <u, F^T v>).
 
@@ -29,7 +29,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda", torch.float64)
 
 
-@pytest.mark.parametrize("dims", [(2, 2, 1), (41, 41, 3), (23, 17, 21), (50, 4, 30)],
+@pytest.mark.parametrize("dims", [(2, 2, 1), (41, 41, 3), (23, 17, 21), (50, 4, 30), (1, 1, 9000)],
                          ids=lambda d: "x".join(map(str, d)))
 def test_filter_one_launch(fe, dims):
     nx, ny, nz = dims
