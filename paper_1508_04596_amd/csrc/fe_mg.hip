@@ -972,6 +972,7 @@ __global__ __launch_bounds__(64) void k_coarse_inverse(int n, int kl, int w,
 #pragma unroll
         for (int c = 0; c < C; ++c) Y[c * n + r] = 0.0;
     ci_sweep<SB / 2 + 1, C, false>(n, kl, Lc, m0, j0, piv, Ud, Y, X);
+    __syncthreads();  // a lane reads the rows that other lanes wrote to Y
     ci_sweep<SB, C, true>(n, w, Uc, 0, j0, piv, Ud, Y, X);
 }
 
