@@ -18,7 +18,7 @@ struct Filter {
     double *b = nullptr, *x = nullptr, *r = nullptr, *p = nullptr, *y = nullptr;
     double *r2 = nullptr, *y2 = nullptr, *s2 = nullptr;  // second buffers of the iteration
     double *partial = nullptr, *sc = nullptr;  // sc: rz, alpha of two iterations, rr, rr0
-    double *hsc = nullptr;                     // pinned host scalars
+    double *hsc = nullptr, *dhsc = nullptr;    // pinned host scalars, their device address
     int last_its = 0;
 };
 hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius);
