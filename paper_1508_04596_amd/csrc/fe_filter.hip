@@ -163,6 +163,14 @@ __device__ __forceinline__ double total(const double *__restrict__ partial, int 
     return v;
 }
 
+// The first workgroup's: the sum of <r, r>'s partials for the host, in pinned memory.
+__device__ __forceinline__ void tell_rr0(const double *__restrict__ prr, int nparts, double *rr0)
+{
+    if (blockIdx.x != 0) return;
+    const double rr = total(prr, nparts);
+    if (threadIdx.x == 0) __hip_atomic_store(rr0, rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sums of a staged plane (u: its tile with the rim) over a node itself, its edge
 // neighbours and its corner neighbours, each weighted by the elements along x and y in
 // common.
@@ -216,6 +224,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_init(FGeo g, CgTiling t, dou
 }
 
 // p = z + beta p_old (z in the first iteration), y = K p, partials of <p, y>.
+// rr0: pinned memory for <r, r> of the start (FIRST).
 // beta = rz / rz_old: rz from the last pass's nparts partials, kept in sc[cur] for the
 // passes that follow; rz_old = sc[1 - cur].
 template <bool FIRST>
@@ -225,7 +234,8 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
                                                           const double *__restrict__ z,
                                                           const double *__restrict__ pold,
                                                           double *__restrict__ p,
-                                                          double *__restrict__ y, double *ppy)
+                                                          double *__restrict__ y, double *ppy,
+                                                          double *rr0)
 {
     __shared__ double w[2][TILE_HALO];  // p of a plane of the tile and its rim, ring of two
     const int sx = t.wx + 2, halo = sx * (t.wy + 2);
@@ -269,7 +279,10 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg_apply(FGeo g, CgTiling t, in
         if (first) {
             const double rz = total(prz, nparts), old = FIRST ? 1.0 : sc[1 - cur];
             if (blockIdx.x == 0 && threadIdx.x == 0) sc[cur] = rz;
-            if (FIRST && !(rz > 0.0)) return;  // the host ends the solve (first_look)
+            if (FIRST) {
+                tell_rr0(prz + RED_BLOCKS, nparts, rr0);
+                if (!(rz > 0.0)) return;  // the host ends the solve (first_look)
+            }
             beta = old > 0.0 ? rz / old : 0.0;
             first = false;
         } else {
@@ -382,17 +395,20 @@ struct CgVec {
 //   beta = rz / rz_old,  alpha = rz / (uw - beta rz / alpha_old),
 //   p = u + beta p,  s = w + beta s,  x += alpha p,  u -= alpha D^-1 s,  w = K u,
 // and the partials of the new rz, uw and <r, r> (out).  rz and alpha are kept in
-// sc[2 cur], sc[2 cur + 1] for the next.  INIT: u = D^-1 b (v.u = b), x = 0.
-// fresh: the first iteration, s = p = 0 are not read.  x is updated every other
+// sc[2 cur], sc[2 cur + 1] for the next.  CG_INIT: u = D^-1 b (v.u = b), x = 0.
+// CG_FIRST: the first iteration, s = p = 0 are not read; rr0: pinned memory for <r, r> of
+// the start.  x is updated every other
 // iteration, with both directions at hand: xmode 0 no, 1 x += alpha p, 2 x +=
 // alpha_old p_old + alpha p.  A zero right-hand side leaves x = 0.
-template <bool INIT>
+enum CgPass { CG_INIT, CG_FIRST, CG_NEXT };
+template <CgPass PASS>
 __global__ __launch_bounds__(RED_THREADS) void k_cg(FGeo g, CgTiling t, int nparts, double iE0,
                                                     const double *__restrict__ partial, double *sc,
-                                                    int cur, int fresh, int xmode, CgVec vec,
-                                                    double *out)
+                                                    int cur, int xmode, CgVec vec,
+                                                    double *out, double *rr0)
 {
     __shared__ double P2[2][TILE_HALO];  // u of a plane of the tile and its rim, ring of two
+    constexpr bool INIT = PASS == CG_INIT, fresh = PASS == CG_FIRST;
     const double E0 = g.E[0];
     const int sx = t.wx + 2, halo = sx * (t.wy + 2);
     constexpr int NL = (TILE_HALO + RED_THREADS - 1) / RED_THREADS;
@@ -472,6 +488,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_cg(FGeo g, CgTiling t, int npar
         } else if (!INIT) {
             double rz, uw;
             totals(partial, nparts, rz, uw);
+            if (fresh) tell_rr0(partial + 2 * RED_BLOCKS, nparts, rr0);
             const double old = fresh ? 0.0 : sc[2 - 2 * cur];
             before = fresh ? 0.0 : sc[3 - 2 * cur];
             beta = old > 0.0 ? rz / old : 0.0;
@@ -574,19 +591,11 @@ static CgTiling cg_tiling(const FGeo &g, bool one)
     return t;
 }
 
-// <r, r> of the start into pinned memory (prr: its partials), over a value that it
-// cannot have.
+// What hsc[5] holds until the first iteration's kernel writes <r, r> of the start there.
 constexpr double RR0_AWAITED = -1.0;
-static int send_rr0(Filter *f, const double *prr, int nb, hipStream_t st)
-{
-    double awaited = RR0_AWAITED;
-    __atomic_store(f->hsc + 5, &awaited, __ATOMIC_RELEASE);
-    FE_CHECK_HIP(launch_reduce(prr, 1, f->sc + 5, nullptr, false, st, nb, f->dhsc + 5));
-    return FE_OK;
-}
 
-// The look at it, taken with the first iteration under way: a zero or non-finite
-// right-hand side ends here with x = 0, not after eight iterations (us per solve, eight /
+// The look at <r, r> of the start, taken with the first iteration under way: a zero or
+// non-finite right-hand side ends here with x = 0, not after eight iterations (us per solve, eight /
 // here: 16^3 122 37, 64x64x128 194 42, 160x160x320 1475 178).  So does one whose target
 // rtol^2 rr0 is below the range of a double: <r, r>, of the same size, would pass as
 // converged when its terms underflow.  FE_PENDING: go on.
@@ -639,16 +648,17 @@ static int solve_one(Filter *f, hipStream_t st, double rtol, int max_its)
     double *part[2] = {f->partial, f->partial + 3 * RED_BLOCKS};
     const double iE0 = 1.0 / g.E[0];
     CgVec v = {f->b, nullptr, nullptr, f->r, f->y, nullptr, f->p, f->x};
-    hipLaunchKernelGGL(k_cg<true>, gb, gt, 0, st, g, t, nb, iE0, (const double *)nullptr, f->sc, 0, 1,
-                       0, v, part[0]);
+    hipLaunchKernelGGL(k_cg<CG_INIT>, gb, gt, 0, st, g, t, nb, iE0, (const double *)nullptr, f->sc, 0,
+                       0, v, part[0], f->dhsc + 5);
     FE_CHECK_HIP(hipGetLastError());
-    int rc = send_rr0(f, part[0] + 2 * RED_BLOCKS, nb, st);
-    if (rc) return rc;
+    int rc;
+    f->hsc[5] = RR0_AWAITED;
     v = {f->r, f->y, f->s2, f->r2, f->y2, f->b, f->p, f->x};
     for (int it = 1; it <= max_its; ++it) {
         const int cur = it & 1;
-        hipLaunchKernelGGL(k_cg<false>, gb, gt, 0, st, g, t, nb, iE0, (const double *)part[1 - cur],
-                           f->sc, cur, it == 1, it % 2 == 0 ? 2 : it == max_its ? 1 : 0, v, part[cur]);
+        hipLaunchKernelGGL(it == 1 ? k_cg<CG_FIRST> : k_cg<CG_NEXT>, gb, gt, 0, st, g, t, nb, iE0,
+                           (const double *)part[1 - cur], f->sc, cur, it % 2 == 0 ? 2 : it == max_its ? 1 : 0, v, part[cur],
+                           f->dhsc + 5);
         FE_CHECK_HIP(hipGetLastError());
         v = {v.un, v.wn, v.sn, const_cast<double *>(v.u), const_cast<double *>(v.w),
              const_cast<double *>(v.s), f->p, f->x};
@@ -672,17 +682,19 @@ static int solve_two(Filter *f, hipStream_t st, double rtol, int max_its)
     hipLaunchKernelGGL(k_cg_init, gb, gt, 0, st, g, t, iE0, (const double *)f->b, f->x, f->r, prz);
     FE_CHECK_HIP(hipGetLastError());
     // sc[0], sc[1]: rz of the last two iterations; sc[2]: alpha of the one before
-    int rc = send_rr0(f, prr, nb, st);
-    if (rc) return rc;
+    int rc;
+    f->hsc[5] = RR0_AWAITED;
     double *pn = f->p, *po = f->b;
     int cur = 0;
     for (int it = 1; it <= max_its; ++it) {
         if (it == 1)
             hipLaunchKernelGGL(k_cg_apply<true>, gb, gt, 0, st, g, t, nb, (const double *)prz, f->sc,
-                               cur, (const double *)f->r, (const double *)po, pn, f->y, ppy);
+                               cur, (const double *)f->r, (const double *)po, pn, f->y, ppy,
+                               f->dhsc + 5);
         else
             hipLaunchKernelGGL(k_cg_apply<false>, gb, gt, 0, st, g, t, nb, (const double *)prz,
-                               f->sc, cur, (const double *)f->r, (const double *)po, pn, f->y, ppy);
+                               f->sc, cur, (const double *)f->r, (const double *)po, pn, f->y, ppy,
+                               f->dhsc + 5);
         if (it % 2 == 0 || it == max_its)
             hipLaunchKernelGGL(k_cg_step<true>, gb, gt, 0, st, g, t, nb, iE0, (const double *)ppy,
                                f->sc, cur, it % 2 == 0, (const double *)po, (const double *)pn,
