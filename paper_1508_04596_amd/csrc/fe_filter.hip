@@ -63,7 +63,15 @@ __device__ __forceinline__ void block_partials(const double *v, double *out)
     }
 }
 
+// Element (i, j, k) in the caller's arrays.  THIN: x and z are exchanged here.
+template <bool THIN>
+__device__ __forceinline__ int64_t elem(const FGeo &g, int i, int j, int k)
+{
+    return THIN ? k + (int64_t)g.nz * (j + (int64_t)g.ny * i) : i + (int64_t)g.nx * (j + (int64_t)g.ny * k);
+}
+
 // node value = scale * sum of the element values around the node (T: h^3/8; A^T: 1/8)
+template <bool THIN>
 __global__ __launch_bounds__(256) void k_elem_to_node(FGeo g, const double *__restrict__ e,
                                                       double scale, double *__restrict__ out)
 {
@@ -79,7 +87,7 @@ __global__ __launch_bounds__(256) void k_elem_to_node(FGeo g, const double *__re
             if (ey < 0 || ey >= g.ny) continue;
             for (int ex = I - 1; ex <= I; ++ex) {
                 if (ex < 0 || ex >= g.nx) continue;
-                acc += e[ex + (int64_t)g.nx * (ey + (int64_t)g.ny * ez)];
+                acc += e[elem<THIN>(g, ex, ey, ez)];
             }
         }
     }
@@ -87,6 +95,7 @@ __global__ __launch_bounds__(256) void k_elem_to_node(FGeo g, const double *__re
 }
 
 // element value = scale * sum of its 8 node values (A: 1/8; T^T: h^3/8)
+template <bool THIN>
 __global__ __launch_bounds__(256) void k_node_to_elem(FGeo g, const double *__restrict__ nv,
                                                       double scale, double *__restrict__ out)
 {
@@ -97,7 +106,7 @@ __global__ __launch_bounds__(256) void k_node_to_elem(FGeo g, const double *__re
     double acc = 0.0;
 #pragma unroll
     for (int b = 0; b < 8; ++b) acc += nv[fnode(g, i + (b & 1), j + ((b >> 1) & 1), k + (b >> 2))];
-    out[e] = scale * acc;
+    out[THIN ? elem<THIN>(g, i, j, k) : e] = scale * acc;
 }
 
 // Work of the CG passes: tiles of wx x wy nodes (at most 256, one per thread) times
@@ -541,9 +550,16 @@ hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
     const double h = grid.h, r = radius / (2.0 * 1.7320508075688772935);
     const double kap[4] = {1.0 / 3.0, 0.0, -1.0 / 12.0, -1.0 / 12.0};
     const double mu[4] = {8.0, 4.0, 2.0, 1.0};
-    f->g.nx = grid.nx;
+    // The passes give a thread to every node of an x-y tile and walk along z, so a column
+    // of few nodes across leaves most threads idle: its x and z are exchanged (the element
+    // matrix does not tell the axes apart, and only the element arrays keep the caller's
+    // order).  us per solve, along z / exchanged: 1x1x9000 961 274, 2x2x40000 1289 443,
+    // 4x4x2000 320 278; 6x6x2000, wide enough, 324 354, and 6x6x60, whose tiles have one
+    // plane, 247 281.
+    f->thin = (int64_t)(grid.nx + 1) * (grid.ny + 1) <= 32 && grid.nz > 512;
+    f->g.nx = f->thin ? grid.nz : grid.nx;
     f->g.ny = grid.ny;
-    f->g.nz = grid.nz;
+    f->g.nz = f->thin ? grid.nx : grid.nz;
     for (int d = 0; d < 4; ++d) f->g.E[d] = r * r * h * kap[d] + h * h * h / 216.0 * mu[d];
     f->nn = (int64_t)(grid.nx + 1) * (grid.ny + 1) * (grid.nz + 1);
     f->ne = (int64_t)grid.nx * grid.ny * grid.nz;
@@ -724,14 +740,15 @@ int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
 
 hipError_t filter_load(Filter *f, const double *gamma, double scale, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_elem_to_node, dim3(nblk(f->nn)), dim3(256), 0, st, f->g, gamma, scale, f->b);
+    hipLaunchKernelGGL(f->thin ? k_elem_to_node<true> : k_elem_to_node<false>, dim3(nblk(f->nn)),
+                       dim3(256), 0, st, f->g, gamma, scale, f->b);
     return hipGetLastError();
 }
 
 hipError_t filter_unload(Filter *f, double scale, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_node_to_elem, dim3(nblk(f->ne)), dim3(256), 0, st, f->g,
-                       (const double *)f->x, scale, out);
+    hipLaunchKernelGGL(f->thin ? k_node_to_elem<true> : k_node_to_elem<false>, dim3(nblk(f->ne)),
+                       dim3(256), 0, st, f->g, (const double *)f->x, scale, out);
     return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@ struct Filter {
     FGeo g;
     int64_t nn = 0, ne = 0;
     double load = 0.0;  // h^3 / 8
+    bool thin = false;  // x and z are exchanged in g
     double *b = nullptr, *x = nullptr, *r = nullptr, *p = nullptr, *y = nullptr;
     double *r2 = nullptr, *y2 = nullptr, *s2 = nullptr;  // second buffers of the iteration
     double *partial = nullptr, *sc = nullptr;  // sc: rz, alpha of two iterations, rr, rr0
