@@ -542,7 +542,8 @@ inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 // Largest grid (nodes) whose iteration is one launch: up to there a pass's latency
 // bounds, above it the rims of the three vectors it stages cost more than the launch (us
 // per solve, two launches / one: 16^3 350 268, 32x32x64 355 290, 48x48x96 387 344, 64^3
-// 396 375, 64x64x96 425 414, 64x64x128 484 503, 96^3 628 943).
+// 396 375, 64x64x96 425 414, 64x64x128 484 503, 96^3 628 943).  Only up to there are its
+// second buffers allocated.
 constexpr int64_t CG_ONE = 300000;
 
 hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius)
@@ -660,7 +661,7 @@ static int solve_one(Filter *f, hipStream_t st, double rtol, int max_its)
     const int nb = std::min(t.tiles, RED_BLOCKS);
     const dim3 gb(nb), gt(RED_THREADS);
     // partials of rz, uw and rr, two sets in turn; sc: rz and alpha of the last two
-    // iterations, then rr and its first value
+    // iterations, then rr
     double *part[2] = {f->partial, f->partial + 3 * RED_BLOCKS};
     const double iE0 = 1.0 / g.E[0];
     CgVec v = {f->b, nullptr, nullptr, f->r, f->y, nullptr, f->p, f->x};
@@ -735,7 +736,7 @@ static int solve_two(Filter *f, hipStream_t st, double rtol, int max_its)
 // returns FE_OK, FE_NOT_CONVERGED or an error
 int filter_solve(Filter *f, hipStream_t st, double rtol, int max_its)
 {
-    return f->nn <= CG_ONE ? solve_one(f, st, rtol, max_its) : solve_two(f, st, rtol, max_its);
+    return f->s2 ? solve_one(f, st, rtol, max_its) : solve_two(f, st, rtol, max_its);
 }
 
 hipError_t filter_load(Filter *f, const double *gamma, double scale, hipStream_t st)

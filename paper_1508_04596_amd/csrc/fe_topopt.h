@@ -17,9 +17,14 @@ struct Filter {
     double load = 0.0;  // h^3 / 8
     bool thin = false;  // x and z are exchanged in g
     double *b = nullptr, *x = nullptr, *r = nullptr, *p = nullptr, *y = nullptr;
-    double *r2 = nullptr, *y2 = nullptr, *s2 = nullptr;  // second buffers of the iteration
-    double *partial = nullptr, *sc = nullptr;  // sc: rz, alpha of two iterations, rr, rr0
-    double *hsc = nullptr, *dhsc = nullptr;    // pinned host scalars, their device address
+    // second buffers of the one-launch iteration, on the grids that it is for (else null:
+    // two launches)
+    double *r2 = nullptr, *y2 = nullptr, *s2 = nullptr;
+    // sc[0..3]: rz and alpha of two iterations (two launches: rz of two iterations, then
+    // alpha of the one before); sc[4]: <r, r>
+    double *partial = nullptr, *sc = nullptr;
+    // pinned host scalars, their device address; hsc[4]: <r, r>, hsc[5]: that of the start
+    double *hsc = nullptr, *dhsc = nullptr;
     int last_its = 0;
 };
 hipError_t filter_alloc(Filter *f, const fe_grid &grid, double radius);
