@@ -46,10 +46,12 @@ constexpr double WLO = 0.5 * (1.0 - QG), WHI = 0.5 * (1.0 + QG);  // linear weig
 
 // 1 / sqrt(a), a > 0: the hardware estimate and one correction step, within one
 // unit in the last place (the error of 1 / sqrt(a) in two rounded operations).
+// |u_e|^2 overflows from |u| = 2e153 on: 1 / sqrt(inf) = 0, where the step's 1 - inf * 0
+// would be NaN (the maximum takes the number).
 __device__ __forceinline__ double rsqrt_n(double a)
 {
     const double r = __builtin_amdgcn_rsq(a);  // relative error < 2^-22
-    const double e = fma(-(a * r), r, 1.0);
+    const double e = fmax(fma(-(a * r), r, 1.0), -1.0);
     return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
@@ -85,8 +87,8 @@ struct Quad {
         y = mm(dy, v, 0.0);
     }
     __device__ __forceinline__ double interp_n(double v) const { return mm(nn, v, 0.0); }
-    // sum over the element's lanes
-    __device__ __forceinline__ double sum(double v) const { return mm(1.0, v, 0.0); }
+    // a sixteenth of the sum over the element's lanes
+    __device__ __forceinline__ double sum16(double v) const { return mm(0.0625, v, 0.0); }
     // corner rows of the Gauss-point terms c, x, y (factors of N, h dN/dx, h dN/dy)
     __device__ __forceinline__ double rows(double c, double x, double y) const
     {
@@ -460,12 +462,12 @@ __device__ __forceinline__ void elem_tile(const Geo &g, const double *__restrict
         m.alpha = S.mat[mb][0][me];
         m.Kc = S.mat[mb][1][me];
         m.s = S.mat[mb][2][me];
-        const double U2 = qd.sum(U2l + U2h) * 0.0625;
+        const double U2 = qd.sum16(U2l + U2h);
         m.tau = rsqrt_n(fma(m.alpha, m.alpha, U2 + pr2));
         m.tauT = rsqrt_n(fma(16.0 * m.Kc, m.Kc, U2));
         m.dtau = m.dtauT = 0.0;
         if (OP == OP_JV) {
-            const double du = qd.sum(dl + dh) * 0.0625;
+            const double du = qd.sum16(dl + dh);
             m.dtau = -(m.tau * m.tau * m.tau) * du;
             m.dtauT = -(m.tauT * m.tauT * m.tauT) * du;
         }
@@ -517,8 +519,7 @@ __device__ __forceinline__ void elem_tile(const Geo &g, const double *__restrict
         }
         double coef = 0.0;
         if (OP == OP_JTV)  // variations of tau and tauT with the element velocity
-            coef = (m.tau * m.tau * m.tau * qd.sum(A) + m.tauT * m.tauT * m.tauT * qd.sum(AT)) *
-                   -0.0625;
+            coef = -(m.tau * m.tau * m.tau * qd.sum16(A) + m.tauT * m.tauT * m.tauT * qd.sum16(AT));
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             double lo = acc.lo[f];
