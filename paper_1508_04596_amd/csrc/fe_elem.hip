@@ -30,20 +30,6 @@
 namespace fe {
 namespace {
 
-// Gauss loop rolled (run-time signs) by default: the unrolled form (compile-time
-// signs, fewer instructions) needs more registers than a wave64 can hold
-// without spilling in FP64, and runs at lower occupancy in FP32.
-#ifndef FE_UNROLL64
-#define FE_UNROLL64 0
-#endif
-#ifndef FE_UNROLL32
-#define FE_UNROLL32 0
-#endif
-template <typename T>
-struct Unroll { static constexpr bool value = FE_UNROLL32 != 0; };
-template <>
-struct Unroll<double> { static constexpr bool value = FE_UNROLL64 != 0; };
-
 template <typename T>
 struct EC {
     T W;        // (h/2)^3, Gauss weight times Jacobian determinant
@@ -138,17 +124,8 @@ __device__ __forceinline__ void to_modal_sel(T f[8], const EC<T> &c)
         to_modal(f, c);
 }
 
-// Signs of the Gauss point coordinates (+1 / -1 per direction) and their
-// products, either as compile-time constants (fully unrolled Gauss loop) or as
-// run-time values (rolled loop, lower register pressure).
-template <int G>
-struct SgCT {
-    static constexpr double sx = (G & 1) ? 1.0 : -1.0;
-    static constexpr double sy = (G & 2) ? 1.0 : -1.0;
-    static constexpr double sz = (G & 4) ? 1.0 : -1.0;
-    static constexpr double sxy = sx * sy, sxz = sx * sz, syz = sy * sz, sxyz = sx * sy * sz;
-};
-
+// Signs of the Gauss point coordinates (+1 / -1 per direction) and their products,
+// as run-time values (rolled Gauss loop).
 template <typename T>
 struct SgRT {
     T sx, sy, sz, sxy, sxz, syz, sxyz;
@@ -204,19 +181,13 @@ __device__ __forceinline__ void accum(const SGT &SG, T Y[8], T c, T Cx, T Cy, T 
     Y[7] += T(SG.sxyz) * e7;
 }
 
-// Run BODY(sg) over the eight Gauss points: unrolled with compile-time signs
-// when UNR, else as a rolled loop with run-time signs.
-#define FE_GAUSS_LOOP(UNR, T, BODY)                                              \
-    if (UNR) {                                                                   \
-        { SgCT<0> sg; BODY(sg) } { SgCT<1> sg; BODY(sg) }                        \
-        { SgCT<2> sg; BODY(sg) } { SgCT<3> sg; BODY(sg) }                        \
-        { SgCT<4> sg; BODY(sg) } { SgCT<5> sg; BODY(sg) }                        \
-        { SgCT<6> sg; BODY(sg) } { SgCT<7> sg; BODY(sg) }                        \
-    } else {                                                                     \
-        _Pragma("unroll 1") for (int g_ = 0; g_ < 8; ++g_) {                     \
-            SgRT<T> sg(g_);                                                      \
-            BODY(sg)                                                             \
-        }                                                                        \
+// Run BODY(sg) over the eight Gauss points: a rolled loop with run-time signs.  Unrolled
+// with compile-time signs, the bodies need more registers than a wave has in FP64 and
+// run at lower occupancy in FP32.
+#define FE_GAUSS_LOOP(T, BODY)                                                   \
+    _Pragma("unroll 1") for (int g_ = 0; g_ < 8; ++g_) {                         \
+        SgRT<T> sg(g_);                                                          \
+        BODY(sg)                                                                 \
     }
 
 // Gauss points in pairs that differ only in the x sign: the sums over the
@@ -415,11 +386,10 @@ __device__ __forceinline__ int opaque_tid()
 // and its mask byte): the box position and the global node index are worked
 // out once for five values.  Fixed trip count, branch-free loads (nodes
 // outside the box or the grid load node 0 and are replaced by 0), all issued
-// before the first wait.  The direction may be stored in another type (Tv)
-// than the state; it is converted to T as it is staged.
-template <typename T, bool HASV, typename Tv = T>
+// before the first wait.
+template <typename T, bool HASV>
 __device__ __forceinline__ void stage_by_node(const Geo &g, const TileIdx &t,
-                                              const T *__restrict__ x, const Tv *__restrict__ v,
+                                              const T *__restrict__ x, const T *__restrict__ v,
                                               const uint8_t *__restrict__ nmask, T (*sx)[BOXN],
                                               T (*sv)[BOXN], int tid)
 {
@@ -440,11 +410,11 @@ __device__ __forceinline__ void stage_by_node(const Geo &g, const TileIdx &t,
             xv[it][f] = in ? xl : T(0);
         }
         if (HASV) {
-            const Tv *vp = v + NF * gn;
+            const T *vp = v + NF * gn;
             const int m = in ? (int)nmask[gn] : 0x1f;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const T vl = (T)vp[f];
+                const T vl = vp[f];
                 vv[it][f] = ((m >> f) & 1) ? T(0) : vl;
             }
         }
@@ -464,9 +434,9 @@ __device__ __forceinline__ void stage_by_node(const Geo &g, const TileIdx &t,
 
 // Stage one value (node and field) per thread and iteration, fixed trip count,
 // branch-free as above.
-template <typename T, bool HASV, typename Tv = T>
+template <typename T, bool HASV>
 __device__ __forceinline__ void stage_by_value(const Geo &g, const TileIdx &t,
-                                               const T *__restrict__ x, const Tv *__restrict__ v,
+                                               const T *__restrict__ x, const T *__restrict__ v,
                                                const uint8_t *__restrict__ nmask, T (*sx)[BOXN],
                                                T (*sv)[BOXN], int tid)
 {
@@ -485,7 +455,7 @@ __device__ __forceinline__ void stage_by_value(const Geo &g, const TileIdx &t,
         xv[it] = in ? xl : T(0);
         vv[it] = T(0);
         if (HASV) {
-            const T vl = (T)v[NF * gn + f];
+            const T vl = v[NF * gn + f];
             const int m = nmask[gn];
             const bool keep = in & (((m >> f) & 1) == 0);
             vv[it] = keep ? vl : T(0);
@@ -505,18 +475,17 @@ __device__ __forceinline__ void stage_by_value(const Geo &g, const TileIdx &t,
 // Stage the node box of x (and of the masked direction v) in LDS; zero the
 // output accumulator.  The FP32 kernels stage by node: that measured 4-5 %
 // faster for the FP32 J v element pass (64^3: 31.2 -> 29.9 us, 160x160x320:
-// 709 -> 675 us).  The FP64 kernels stage by value: by node, J v and J^T w did
-// not change and the residual, whose body then no longer fits two waves per
-// SIMD, ran 18-23 % slower.
-template <typename T, int NVO, bool HASV, typename Tv = T>
+// 709 -> 675 us).  The FP64 kernels here (design derivative, nodal blocks) stage by
+// value, whose loads are contiguous.
+template <typename T, int NVO, bool HASV>
 __device__ __forceinline__ void stage(const Geo &g, const TileIdx &t, const T *__restrict__ x,
-                                      const Tv *__restrict__ v, const uint8_t *__restrict__ nmask,
+                                      const T *__restrict__ v, const uint8_t *__restrict__ nmask,
                                       T (*sx)[BOXN], T (*sv)[BOXN], T *so)
 {
     if constexpr (sizeof(T) == 4)
-        stage_by_node<T, HASV, Tv>(g, t, x, v, nmask, sx, sv, opaque_tid());
+        stage_by_node<T, HASV>(g, t, x, v, nmask, sx, sv, opaque_tid());
     else
-        stage_by_value<T, HASV, Tv>(g, t, x, v, nmask, sx, sv, (int)threadIdx.x);
+        stage_by_value<T, HASV>(g, t, x, v, nmask, sx, sv, (int)threadIdx.x);
     if (NVO > 0)
         for (int idx = threadIdx.x; idx < BOXN * NVO; idx += NTHR) so[idx] = T(0);
 }
@@ -524,7 +493,7 @@ __device__ __forceinline__ void stage(const Geo &g, const TileIdx &t, const T *_
 // ---- element bodies -------------------------------------------------------------
 
 // Residual rows of one element (Galerkin + SUPG + PSPG, see header comment).
-template <typename T, bool UNR>
+template <typename T>
 __device__ __forceinline__ void elem_residual(const EC<T> &c, const T (*sx)[BOXN], const int nb[8],
                                               T alpha, T Kc, T s, T out[NF][8])
 {
@@ -600,7 +569,7 @@ __device__ __forceinline__ void elem_residual(const EC<T> &c, const T (*sx)[BOXN
 // which halves the residual's occupancy (2 -> 1 workgroup per CU); it ran 24 %
 // slower.
 #define FE_RES_GP(SG) { FE_RES_EVAL1(SG) FE_RES_POINT(SG, V1_) }
-    FE_GAUSS_LOOP(UNR, T, FE_RES_GP)
+    FE_GAUSS_LOOP(T, FE_RES_GP)
 #undef FE_RES_EVAL1
 #undef FE_RES_POINT
 #undef FE_RES_GP
@@ -610,11 +579,11 @@ __device__ __forceinline__ void elem_residual(const EC<T> &c, const T (*sx)[BOXN
 
 // Directional derivative J_e v_e (exact linearisation, including d tau).
 // xs(f, a), vs(f, a): the state and the direction at corner a, field f.
-template <typename T, bool UNR, typename XS, typename VS>
+template <typename T, typename XS, typename VS>
 __device__ __forceinline__ void elem_jv(const EC<T> &c, XS xs, VS vs, T alpha, T Kc, T s,
                                         T out[NF][8])
 {
-    constexpr bool PG = !UNR && FE_GP_PAIRS;  // paired Gauss points: gs-scaled modes
+    constexpr bool PG = FE_GP_PAIRS;  // paired Gauss points: gs-scaled modes
     T mu[3][8], md[3][8], mp[8], mT[8], mdp[8], mdT[8];
     T U2 = T(0), udu = T(0);
 #pragma unroll
@@ -717,8 +686,8 @@ __device__ __forceinline__ void elem_jv(const EC<T> &c, XS xs, VS vs, T alpha, T
             Kc * gdT[1] + u[1] * AT + du[1] * BT, Kc * gdT[2] + u[2] * AT + du[2] * BT)      \
     }
 #define FE_JV_GP(SG) { FE_JV_EVAL1(SG) FE_JV_POINT(SG, V1_, FE_ACC_NOW) }
-    if (UNR || !FE_GP_PAIRS) {
-        FE_GAUSS_LOOP(UNR, T, FE_JV_GP)
+    if (!FE_GP_PAIRS) {
+        FE_GAUSS_LOOP(T, FE_JV_GP)
     } else {
         FE_GAUSS_PAIRS(T, FE_JV_EVAL2, FE_JV_POINT)
     }
@@ -735,11 +704,11 @@ __device__ __forceinline__ void elem_jv(const EC<T> &c, XS xs, VS vs, T alpha, T
 // (temperature rows) are interpolated from w_e; the multipliers of the varied
 // strong residuals are mu = tau (u.grad Lambda + grad Pi) and muT = tauT u.grad Theta;
 // the element-level tau variation is applied after the Gauss loop.
-template <typename T, bool UNR>
+template <typename T>
 __device__ __forceinline__ void elem_jtv(const EC<T> &c, const T (*sx)[BOXN], const T (*sv)[BOXN],
                                          const int nb[8], T alpha, T Kc, T s, T out[NF][8])
 {
-    constexpr bool PG = !UNR && FE_GP_PAIRS;  // paired Gauss points: gs-scaled modes
+    constexpr bool PG = FE_GP_PAIRS;  // paired Gauss points: gs-scaled modes
     T mu[3][8], mL[3][8], mp[8], mT[8], mP[8], mTh[8];
     T U2 = T(0);
 #pragma unroll
@@ -842,8 +811,8 @@ __device__ __forceinline__ void elem_jtv(const EC<T> &c, const T (*sx)[BOXN], co
             Kc * gTh[0] + ThM * u[0], Kc * gTh[1] + ThM * u[1], Kc * gTh[2] + ThM * u[2])    \
     }
 #define FE_JTV_GP(SG) { FE_JTV_EVAL1(SG) FE_JTV_POINT(SG, V1_, FE_ACC_NOW) }
-    if (UNR || !FE_GP_PAIRS) {
-        FE_GAUSS_LOOP(UNR, T, FE_JTV_GP)
+    if (!FE_GP_PAIRS) {
+        FE_GAUSS_LOOP(T, FE_JTV_GP)
     } else {
         FE_GAUSS_PAIRS(T, FE_JTV_EVAL2, FE_JTV_POINT)
     }
@@ -885,15 +854,14 @@ __device__ __forceinline__ void elem_tile(const Geo &g, const float *__restrict_
         const int64_t e = (int64_t)t.i + (int64_t)g.nx * ((int64_t)t.j + (int64_t)g.ny * t.k);
         const double y = gamma[e];
         const T alpha = (T)alpha_of(g, y), Kc = (T)K_of(g, y), s = (T)src[e];
-        constexpr bool UNR = Unroll<T>::value;
         if (OP == OP_RES)
-            elem_residual<T, UNR>(c, S.x, t.nb, alpha, Kc, s, R);
+            elem_residual<T>(c, S.x, t.nb, alpha, Kc, s, R);
         else if (OP == OP_JV)
-            elem_jv<T, UNR>(
+            elem_jv<T>(
                 c, [&](int f, int a) { return S.x[f][t.nb[a]]; },
                 [&](int f, int a) { return S.v[f][t.nb[a]]; }, alpha, Kc, s, R);
         else
-            elem_jtv<T, UNR>(c, S.x, S.v, t.nb, alpha, Kc, s, R);
+            elem_jtv<T>(c, S.x, S.v, t.nb, alpha, Kc, s, R);
     }
     // ordered accumulation: in sub-step a every thread adds its corner-a row
     // to a distinct node of the box
@@ -1152,7 +1120,6 @@ __global__ __launch_bounds__(NTHR) void k_dRdgamma(Geo g, const double *__restri
                                                    double *__restrict__ gout)
 {
     using T = double;
-    constexpr bool UNR = Unroll<T>::value;
     __shared__ T sx[NF][BOXN];
     __shared__ T sl[NF][BOXN];
     const TileIdx t = tile_index(g);
@@ -1218,7 +1185,7 @@ __global__ __launch_bounds__(NTHR) void k_dRdgamma(Geo g, const double *__restri
         T uTh = u[0] * gTh[0] + u[1] * gTh[1] + u[2] * gTh[2];                               \
         gk += gTh[0] * gT[0] + gTh[1] * gT[1] + gTh[2] * gT[2] + dtauT_dK * uTh * rT;        \
     }
-    FE_GAUSS_LOOP(UNR, T, FE_DG_GP)
+    FE_GAUSS_LOOP(T, FE_DG_GP)
 #undef FE_DG_GP
     gout[e] = c.W * (da * ga + dK * gk);
 }
@@ -1432,7 +1399,7 @@ __global__ __launch_bounds__(NTHR, BdCfg<T>::WAVES) void k_blockdiag(Geo g, cons
             bd_corner(c, st, N, dN, ua[cc], alpha, Kc, tau, tauT, blk[cc]);                   \
         }                                                                                    \
     }
-            FE_GAUSS_LOOP(false, T, FE_BD2_GP)
+            FE_GAUSS_LOOP(T, FE_BD2_GP)
 #undef FE_BD2_GP
         }
 #pragma unroll
@@ -1541,7 +1508,7 @@ __global__ __launch_bounds__(64) void k_elem_jac(Geo g, const double *__restrict
     const double y = gamma[e];
     const double alpha = alpha_of(g, y), Kc = K_of(g, y), s = src[e];
     double R[NF][8];
-    elem_jv<double, false>(
+    elem_jv<double>(
         c, [&](int f, int a) { return x[NF * nd[a] + f]; },
         [&](int f, int a) { return (8 * f + a == col) ? one : 0.0; }, alpha, Kc, s, R);
 #pragma unroll

@@ -601,7 +601,13 @@ hipError_t launch_elem64_pass(ElemOp op, const Geo &g, const double *x, const Tv
                               double *out, double *slots, hipStream_t st)
 {
     switch (op) {
-    case OP_RES: launch<OP_RES, Tv>(g, x, v, gamma, s, nmask, out, slots, st); break;
+    case OP_RES:
+        // (no direction: the shared-node pass is asked for the state's type)
+        if constexpr (sizeof(Tv) == sizeof(double)) {
+            launch<OP_RES, Tv>(g, x, v, gamma, s, nmask, out, slots, st);
+            break;
+        }
+        return hipErrorInvalidValue;
     case OP_JV: launch<OP_JV, Tv>(g, x, v, gamma, s, nmask, out, slots, st); break;
     case OP_JTV: launch<OP_JTV, Tv>(g, x, v, gamma, s, nmask, out, slots, st); break;
     }
