@@ -22,17 +22,21 @@ int hip_fail(hipError_t e, const char *what)
 // Two 256-thread workgroups of the FP64 passes fit a CU, 512 the chip.  Layers cost
 // 3.8 us each while two workgroups share a CU, a workgroup's start and end about
 // 6 us, so a grid that one round of workgroups can cover gets just enough layers
-// per tile for that (J v, us at 1 / 2 / 3 / 4 / 8 layers: 32^3 13.8 13.2 15.0 17.1
-// 26.3, 40^3 21.3 17.4 20.9, 48^3 32.3 28.7 29.5 26.3 27.7, 64^3 63.1 50.4 50.6
-// 45.0 42.8).  Larger grids take 8 layers, or 16 where eight rounds or more keep the
-// last one's share small (96^3, 4 / 8 / 16 layers: 134 126 137; 160x160x320: 1181
+// per tile for that (J v, us at 1 / 2 / 3 / 4 / 8 layers: 40^3 21.3 17.4 20.9, 48^3 32.3
+// 28.7 29.5 26.3 27.7, 64^3 63.1 50.4 50.6 45.0 42.8).  A workgroup that has its CU to
+// itself takes 2.1 us for a second layer, so where tiles of one layer are more than the
+// 256 CUs and tiles of two are not, two it is (1 / 2 layers: 28^3 12.4 12.0, 32^3 13.0
+// 12.3, 40x40x20 13.0 12.3; below, 24^3 9.8 11.8, and where tiles of two still share CUs,
+// 96x64x5 12.8 15.6).  Larger grids take 8 layers, or 16 where eight rounds or more keep
+// the last one's share small (96^3, 4 / 8 / 16 layers: 134 126 137; 160x160x320: 1181
 // 1093 1056).
 int elem_layers(int nx, int ny, int nz)
 {
-    const int64_t round = 512;
+    const int64_t round = 512, cus = 256;
     const int64_t cols = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
     if (cols <= round) {
         const int64_t chunks = round / cols, tz = (nz + chunks - 1) / chunks;
+        if (tz == 1 && cols * nz > cus && cols * ((nz + 1) / 2) <= cus) return 2;
         if (tz <= 16) return (int)tz;
     }
     const int most = cols * ((nz + 15) / 16) >= 8 * round ? 16 : 8;
