@@ -226,9 +226,7 @@ def main():
     t_elem32 = float(np.median([q["t_elem32"] for q in recs]))
     bytes_alg = jv_bytes(n_nodes, n_el)
     achieved = FLOPS_PER_ELEM_JV * n_el / t_elem64
-    # the traffic counters were taken per workload, for one source of the kernel
-    traffic = elem_traffic_bytes(args.config, ELEM64_COUNTERS_KIB) if elem_source_sha256() == \
-        ELEM_TRAFFIC_SRC_SHA256 else None
+    traffic = reported_traffic(args.config)
     n_tiles = -(-p.nx // 8) * -(-p.ny // 8) * -(-p.nz // 4)
     roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VALU / 1e12,
             "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_VALU,
@@ -360,6 +358,14 @@ def serve_trace(fe, inputs, n, budget_gb, max_active, rate=20.0, batched=False,
             "mode": "batched" if batched else "default",
             "engine_steps": steps, "engine_launches": launches,
             "queue_wait_p50_s": float(np.percentile([b - a for a, b, _ in times], 50))}
+
+
+def reported_traffic(config):
+    """Bytes per launch of the FP64 J v element pass: the counters were taken per
+    workload, for one source of the kernel; null for any other."""
+    if elem_source_sha256() != ELEM_TRAFFIC_SRC_SHA256:
+        return None
+    return elem_traffic_bytes(config, ELEM64_COUNTERS_KIB)
 
 
 def elem_source_sha256():
