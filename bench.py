@@ -54,7 +54,7 @@ PEAK_HBM = 8.0e12
 # x 1.951, writes x 1.000.  Workloads without counters report null.  The first
 # figures are those of the pass with one lane per element, for comparison.
 ELEM_COUNTERS_KIB = {2: (14235.56, 17217.22), 3: (474297.2, 537499.9)}
-ELEM64_COUNTERS_KIB = {2: (14161.38, 15801.72), 3: (441132.38, 470602.19)}
+ELEM64_COUNTERS_KIB = {2: (14159.38, 15801.92), 3: (441149.62, 470574.44)}
 FETCH_SCALE, WRITE_SCALE = 1.951, 1.000
 
 
@@ -65,7 +65,7 @@ def elem_traffic_bytes(config, counters=ELEM_COUNTERS_KIB):
 
 # SHA-256 of csrc/fe_elem64.hip when those counters were taken: any other source
 # of the element kernel reports traffic as null instead of a stale figure.
-ELEM_TRAFFIC_SRC_SHA256 = "690284ef59346f179f3ccf80d44620bde77f657f718b5a836efd166032eeab6d"
+ELEM_TRAFFIC_SRC_SHA256 = "4b4d4037574d53f9f83483539915c9a6a565cd21e9819f65a3716545ebd0cad5"
 SOLVES = "Newton to 1e-8 FP64, mixed and FP64 with an FP32 preconditioner"
 WORKLOADS = {
     2: "C2: 64x64x64 elements (1,373,125 DOF), Gr=1e4, 40% solid smoothed random design; "

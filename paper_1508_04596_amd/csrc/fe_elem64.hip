@@ -12,7 +12,7 @@
 // per SIMD, with nothing to issue while it waits, and 750 moves to and from the
 // accumulation registers per element: 51.9 us for J v at 64^3 and 1.495 ms at
 // 160x160x320.  A quarter of the state fits 256 registers, two waves share a SIMD
-// and cover each other's waits: 40.5 us and 0.94 ms (residual 0.86 -> 0.70 ms,
+// and cover each other's waits: 38.5 us and 0.94 ms (residual 0.86 -> 0.70 ms,
 // J^T w 1.54 -> 1.00 ms), about 82 % of the issue slots of the layer loop in use.
 // What bounds it is FP64 issue: the matrix unit does not run beside the vector
 // unit (32 fma take 154 cycles of a SIMD, 8 of these products 138, both together
